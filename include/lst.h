@@ -139,8 +139,8 @@ int lst_step(lst_state* s, int32_t m, int32_t K, const float* H, const int32_t* 
  * gives the update of V (eq. updateV); Q and U move as in lst_step.  Same
  * arguments, outputs and device errors (LST_ESINGULAR: a zero pivot of U_new).
  * Requires d <= 1024 (LST_EINVAL otherwise).  Never captured into graphs; drift
- * control does not run (it needs U^{-T}).  Allocates its workspace (d^2 +
- * m_max d floats, 2 d ints) at the first call.  Afterwards the state's U^{-T}
+ * control does not run (it needs U^{-T}).  Allocates its workspace (about d^2 +
+ * 32 d floats, 3 d ints) at the first call.  Afterwards the state's U^{-T}
  * no longer matches U: lst_step, lst_stabilize and lst_stabilize_noalloc
  * return LST_ESTATE until lst_restore (which sets U = U^{-T} = I).
  */

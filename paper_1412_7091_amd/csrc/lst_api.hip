@@ -58,11 +58,11 @@ struct lst_state {
   int hbits = 0;
   int ld0 = 0;
   float* on_ws = nullptr;  // single-example step workspace
-  // solve-from-scratch step: A = U_new^T and its LU factors, pivots, the
-  // permutation, Z^T; allocated at its first call.  uit_stale: U^{-T} no
+  // solve-from-scratch step: A = U_new^T and its LU factors, the inverses of
+  // their diagonal blocks, pivots, active rows; allocated at its first call.  uit_stale: U^{-T} no
   // longer matches U (lst_step refuses the state until lst_restore).
-  float *lu_F = nullptr, *lu_Z = nullptr;
-  int *lu_ipiv = nullptr, *lu_perm = nullptr;
+  float *lu_F = nullptr, *lu_dinv = nullptr;
+  int *lu_piv = nullptr, *lu_act = nullptr;
   int uit_stale = 0;
   float* Nm = nullptr;  // m_max > 128: m x ldn, N = A C1 A + A C2 B + B C2^T A + B Y^T Y B
   int ldn = 0;
@@ -276,6 +276,7 @@ int common_init(lst_state* s, int64_t D, int32_t d, const lst_config* cfg, void*
   s->stream = static_cast<hipStream_t>(hip_stream);
   HIPCHK(hipStreamCreateWithFlags(&s->cap, hipStreamNonBlocking));
   HIPCHK(configure_kernels());
+  HIPCHK(lu_configure());
   OK_OR_RETURN(scratch_device_ptr(s->device, &s->scratch));
   OK_OR_RETURN(dalloc(s, &s->flags, F_COUNT));
   HIPCHK(hipMemsetAsync(s->flags, 0, F_COUNT * sizeof(int), s->stream));
@@ -611,10 +612,10 @@ int enqueue_step(lst_state* s, hipStream_t st, int32_t m, int32_t K, const float
       F.gemm.p[0].tile = 64;
       HIPCHK(step_launch(c, F, stages_for(F.gemm, kLaunch34Stages), st));
     }
-    HIPCHK(lu_factor(s->lu_F, d, s->lu_ipiv, s->lu_perm, fl, st));
+    HIPCHK(lu_factor(s->lu_F, d, s->lu_piv, s->lu_act, s->lu_dinv, fl, st));
     OK_OR_RETURN(prof_mark(s, PH_SCRATCH_FACTOR, 1, st));
     OK_OR_RETURN(prof_mark(s, PH_SCRATCH_SOLVE, 0, st));
-    HIPCHK(lu_solve_rows(s->lu_F, s->lu_perm, d, H, m, s->lu_Z, s->X, s->a, lr, st));
+    HIPCHK(lu_solve_rows(s->lu_F, s->lu_piv, s->lu_dinv, d, H, m, s->X, s->a, lr, st));
     if (shifted) HIPCHK(shift_terms(c, m <= 128, false, true, st));
     OK_OR_RETURN(prof_mark(s, PH_SCRATCH_SOLVE, 1, st));
     StepLaunch L{};
@@ -951,8 +952,8 @@ int lst_step_solve(lst_state* s, int32_t m, int32_t K, const float* H, const int
   if (!s->lu_F) {
     const int d = s->d;
     if ((rc = dalloc(s, &s->lu_F, (size_t)d * d)) ||
-        (rc = dalloc(s, &s->lu_Z, (size_t)s->cfg.m_max * d)) || (rc = dalloc(s, &s->lu_ipiv, d)) ||
-        (rc = dalloc(s, &s->lu_perm, d)))
+        (rc = dalloc(s, &s->lu_dinv, lu_dinv_floats(d))) || (rc = dalloc(s, &s->lu_piv, d)) ||
+        (rc = dalloc(s, &s->lu_act, 2 * (size_t)d)))
       return rc;
   }
   if (s->prof) s->prof_steps += 1;

@@ -3,415 +3,569 @@
 // through the Woodbury identity, factor A = U_new^T every step and solve
 // A z_i = h_i for the m examples of the minibatch, O(d^3) + O(m d^2) work.
 //
-// Factorisation (right-looking, partial pivoting, P A = L R): panels of 32
-// columns.  Per panel three launches:
-//   lu_panel_kernel  one workgroup factors the panel (rows j0 .. d) in
-//                    registers: per column an arg-max over the rows (ties to
-//                    the lower row), the swap, the multipliers and the rank-1
-//                    update of the panel's remaining columns;
-//   lu_apply_kernel  every other column: the panel's row interchanges (the
-//                    rows involved staged in LDS), then right of the panel the
-//                    forward substitution with the panel's unit lower triangle;
-//   trailing update  A22 -= L21 U12 on the library's 128 x 128 MFMA tiles.
-// Row solves, in the examples' row layout (row i of X holds z_i^T): with
-// P A = L R, A z = h is z = R^{-1} L^{-1} P h.  Column blocks of 64 go forward
-// through L (unit lower, ascending) and back through R (descending); each
-// block first takes the product with the entries already solved, then solves
-// its 64 x 64 triangle.  The last pass writes X_i = -lr a_i z_i, the form the
-// step's scatter consumes.
+// Both halves are chains: d pivots one after another, then twice d / 16 blocks
+// of unknowns, so what counts is the time of one link and not the flops.
+//
+// Factorisation (right-looking, partial pivoting, P A = L R), panels of 32
+// columns, one launch per panel.  Rows are never interchanged: piv[k] names
+// the row of A chosen at step k, act lists the rows not chosen yet (ascending),
+// and every access to a row goes through one of the two.  Launch p applies
+// panel p - 1 to everything on its right and factors panel p:
+//   block 0        the columns of panel p: U12 by substitution, the rank-32
+//                  update on MFMA, then the panel itself with one active row
+//                  per thread (registers);
+//   blocks 1 ..    32 columns each of the panels after p: U12 and the update;
+//   last block     inverses of the 16 x 16 diagonal blocks of panel p - 1 for
+//                  the row solves.
+// Factoring a panel is a chain of 32 links.  A link: the largest |a| of the
+// column per wave (DPP, no LDS), its row published in LDS by the lane that
+// holds it, one barrier, the wave holding the largest found by every wave for
+// itself, the row read back as a broadcast, the rank-1 update.  The column in
+// hand is always register 0 (the update shifts the row by one register), so
+// a link is one loop body.
+//
+// Row solves, P A = L R: A z = h is z = R^{-1} L^{-1} P h.  A workgroup solves
+// for 16 examples; its waves hold the right-hand sides as MFMA accumulators
+// (16 unknowns x 16 examples a block) and go through the blocks once forward
+// and once back.  A link: the owner multiplies its block by the inverse of the
+// diagonal block (an accumulator has the layout of an MFMA's B operand, so no
+// data moves between lanes), publishes it in LDS, one barrier, and every wave
+// subtracts the block's part from the blocks it owns, the factor's fragments
+// loaded several links ahead.
+//
+// At d = 500, m = 128: 480 us for the factorisation (16 launches of 25 to 34
+// us, a link about 0.75 us; 1.4 ms when a link was three barriers and ten
+// shuffles and the interchanges and the update were launches of their own)
+// and 47 us for the solves (0.5 ms with a launch per 64 unknowns on m / 16
+// workgroups).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include "gemm_tile.h"
 #include "lst_internal.h"
 
 namespace lst {
 
 namespace {
 
-constexpr int kLuNB = 32;            // panel width
-constexpr int kSolveNB = 64;         // column block of the row solves
-constexpr int kSolveRows = 16;       // rows of X per workgroup of the row solves
+constexpr int kNB = 32;        // panel width
+constexpr int kSub = 16;       // diagonal blocks of the row solves
+constexpr int kLdT = 36;       // row stride of the 32 x 32 blocks in LDS (16-byte rows)
+constexpr int kRB = 4;         // 16-row blocks of a wave in the rank-32 update
 
-// Panel: columns j0 .. j0 + nc of rows j0 .. d - 1.  Row j0 + t lives in the
-// registers of thread t (1024 threads: d <= 1024); per column only the pivot
-// row and the arg-max partials go through LDS.  Each column is its own
-// template instance, so every register index is a constant.
-constexpr int kPanelThreads = kLuMaxD;
-
-struct PanelShared {
-  float best[kPanelThreads / 64];
-  int bidx[kPanelThreads / 64];
-  int p;
-  int piv[kLuNB];  // the panel's pivot rows, written to ipiv at the end
-  float prow[kLuNB];
-  float old[kLuNB];
+// LDS of a panel launch of nt threads: the panel, column by column (the
+// updated columns on their way from MFMA layout to a row per thread, then the
+// multipliers), and the small blocks.
+struct PanelSmall {
+  float L11[kNB][kLdT];        // multipliers of the previous panel's pivot rows
+  float U12T[kNB][kLdT];       // U12, a row per column
+  float slot[2][16][kLdT];     // each wave's candidate row (by parity of the link)
+  unsigned skey[2][16];
+  int prow[kNB];               // rows of the previous panel's pivots
+  int wcnt[16];
 };
-
-template <int C>
-struct PanelColumn {
-  __device__ __forceinline__ static void run(float (&a)[kLuNB], PanelShared& sh, int d, int j0,
-                                             int nc, int* ipiv, int* flags) {
-    if (C < nc) {
-      const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-      const int r = j0 + tid, rc = j0 + C;
-      // the largest |a| in column C over rows >= rc (ties to the lower row; a
-      // NaN counts as infinite)
-      float best = -1.f;
-      int bidx = 0x7fffffff;
-      if (r < d && r >= rc) {
-        best = fabsf(a[C]);
-        if (best != best) best = INFINITY;
-        bidx = r;
-      }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const float ob = __shfl_xor(best, off);
-        const int oi = __shfl_xor(bidx, off);
-        if (ob > best || (ob == best && oi < bidx)) {
-          best = ob;
-          bidx = oi;
-        }
-      }
-      if (lane == 0) {
-        sh.best[w] = best;
-        sh.bidx[w] = bidx;
-      }
-      __syncthreads();
-      if (tid < 64) {
-        float b = tid < kPanelThreads / 64 ? sh.best[tid] : -1.f;
-        int bi = tid < kPanelThreads / 64 ? sh.bidx[tid] : 0x7fffffff;
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-          const float ob = __shfl_xor(b, off);
-          const int oi = __shfl_xor(bi, off);
-          if (ob > b || (ob == b && oi < bi)) {
-            b = ob;
-            bi = oi;
-          }
-        }
-        if (tid == 0) {
-          sh.p = bi;
-          sh.piv[C] = bi;
-        }
-      }
-      __syncthreads();
-      const int p = sh.p;
-      if (r == p) {
-#pragma unroll
-        for (int cc = 0; cc < kLuNB; ++cc) sh.prow[cc] = a[cc];
-      }
-      if (r == rc && p != rc) {
-#pragma unroll
-        for (int cc = 0; cc < kLuNB; ++cc) sh.old[cc] = a[cc];
-      }
-      __syncthreads();
-      if (p != rc) {
-        if (r == rc) {
-#pragma unroll
-          for (int cc = 0; cc < kLuNB; ++cc) a[cc] = sh.prow[cc];
-        } else if (r == p) {
-#pragma unroll
-          for (int cc = 0; cc < kLuNB; ++cc) a[cc] = sh.old[cc];
-        }
-      }
-      const float piv = sh.prow[C];
-      if (tid == 0 && (!(fabsf(piv) > 0.f) || !isfinite(piv)))
-        atomicCAS(flags + F_ERR, 0, LST_ESINGULAR);
-      if (r < d && r > rc) {
-        const float l = a[C] * (1.f / piv);
-        a[C] = l;
-#pragma unroll
-        for (int cc = C + 1; cc < kLuNB; ++cc) a[cc] -= l * sh.prow[cc];
-      }
-      __syncthreads();  // the pivot row buffers are rewritten for the next column
-    }
-    PanelColumn<C + 1>::run(a, sh, d, j0, nc, ipiv, flags);
-  }
-};
-template <>
-struct PanelColumn<kLuNB> {
-  __device__ __forceinline__ static void run(float (&)[kLuNB], PanelShared&, int, int, int, int*,
-                                             int*) {}
-};
-
-__global__ __launch_bounds__(kPanelThreads) void lu_panel_kernel(float* A, int d, int j0,
-                                                                 int* ipiv, int* flags) {
-  __shared__ PanelShared sh;
-  const int r = j0 + threadIdx.x;
-  const int nc = min(kLuNB, d - j0);
-  float a[kLuNB];
-#pragma unroll
-  for (int c = 0; c < kLuNB; ++c) a[c] = (r < d && c < nc) ? A[(size_t)r * d + j0 + c] : 0.f;
-  PanelColumn<0>::run(a, sh, d, j0, nc, ipiv, flags);
-  if (threadIdx.x < nc) ipiv[j0 + threadIdx.x] = sh.piv[threadIdx.x];
-  if (r < d)
-#pragma unroll
-    for (int c = 0; c < kLuNB; ++c)
-      if (c < nc) A[(size_t)r * d + j0 + c] = a[c];
+__host__ __device__ inline size_t panel_lds_bytes(int nt) {
+  return (size_t)kNB * (nt + 4) * sizeof(float) + sizeof(PanelSmall);
 }
 
-// Columns 64 b .. 64 b + 63 outside the panel: the panel's interchanges in
-// order (the rows they touch staged in LDS), then, right of the panel, the
-// forward substitution with the unit lower triangle L11.  The block after the
-// last column slab applies the same interchanges to perm (the row order of the
-// right-hand sides).
-__global__ __launch_bounds__(64) void lu_apply_kernel(float* A, int d, int j0, const int* ipiv,
-                                                      int* perm) {
-  __shared__ int s_rows[2 * kLuNB];
-  __shared__ int s_slot[kLuNB];
-  __shared__ int s_n;
-  __shared__ float S[2 * kLuNB][65];
-  __shared__ int Sp[2 * kLuNB];
-  __shared__ float Ls[kLuNB][kLuNB + 1];
-  const int tid = threadIdx.x;
-  const int nc = min(kLuNB, d - j0);
-  __shared__ int s_piv[kLuNB];
-  const bool perm_block = blockIdx.x == gridDim.x - 1;
-  const int col = blockIdx.x * 64 + tid;
-  if (tid < nc) s_piv[tid] = ipiv[j0 + tid];
-  __syncthreads();
-  if (tid == 0) {
-    int n = nc;
-    for (int k = 0; k < nc; ++k) s_rows[k] = j0 + k;
-    for (int k = 0; k < nc; ++k) {
-      const int p = s_piv[k];
-      int slot = -1;
-      if (p < j0 + nc) {
-        slot = p - j0;
-      } else {
-        for (int u = nc; u < n; ++u)
-          if (s_rows[u] == p) slot = u;
-        if (slot < 0) {
-          s_rows[n] = p;
-          slot = n++;
-        }
-      }
-      s_slot[k] = slot;
+__device__ __forceinline__ unsigned dpp_max(unsigned v, unsigned o) { return v > o ? v : o; }
+// Largest v of each row of 16 lanes, in all of them.
+__device__ __forceinline__ unsigned row_max16(unsigned v) {
+  v = dpp_max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false));
+  v = dpp_max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false));
+  v = dpp_max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xf, 0xf, false));
+  v = dpp_max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xf, 0xf, false));
+  return v;
+}
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+  v = row_max16(v);
+  const unsigned a = (unsigned)__builtin_amdgcn_readlane((int)v, 0);
+  const unsigned b = (unsigned)__builtin_amdgcn_readlane((int)v, 16);
+  const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)v, 32);
+  const unsigned e = (unsigned)__builtin_amdgcn_readlane((int)v, 48);
+  return dpp_max(dpp_max(a, b), dpp_max(c, e));
+}
+
+// Four floats at p (16-byte aligned when VEC).
+template <bool VEC>
+__device__ __forceinline__ floatx4 load4(const float* p) {
+  if (VEC) return *reinterpret_cast<const floatx4*>(p);
+  return floatx4{p[0], p[1], p[2], p[3]};
+}
+
+// What one launch works on (the panel at column j0 has R = d - j0 active rows).
+struct LuArgs {
+  float* A;
+  int d, j0;
+  int* piv;         // d: row chosen at step k
+  const int* act;   // R: the active rows, ascending
+  int* act_next;    // R - 32 of them after this panel
+  float* dinv;      // per 16-block: L_kk^{-1}, then R_kk^{-1} (256 floats each)
+  int* flags;
+};
+
+// Inverses of the two 16 x 16 diagonal blocks of L and of R at column q0, by
+// one wave: lane 16 b + n holds column n of inverse b (L, L, R, R).  R is
+// taken from its last row up, which makes it a lower triangle too.  Rows past
+// d are those of the identity.
+__device__ void diag_inverses(const LuArgs& a, int q0, PanelSmall& sm) {
+  const int lane = threadIdx.x & 63, n = lane & 15, sub = (lane >> 4) & 1;
+  const bool low = lane < 32;
+  const int nv2 = min(kNB, a.d - q0);  // rows of the panel
+  {
+    // the panel's 32 x 32 block in pivot order (a wave's LDS accesses complete
+    // in order), the identity past its end
+    const int c = lane & 31;
+    for (int i = lane >> 5; i < kNB; i += 2) {
+      const float v = a.A[(size_t)a.piv[q0 + min(i, nv2 - 1)] * a.d + q0 + min(c, nv2 - 1)];
+      sm.L11[i][c] = (i < nv2 && c < nv2) ? v : (i == c ? 1.f : 0.f);
     }
-    s_n = n;
+    asm volatile("" ::: "memory");
   }
-  if (!perm_block) {
-    for (int e0 = 0; e0 < kLuNB * kLuNB; e0 += 8 * 64) {
-      float v[8];
+  if (kSub * sub >= nv2) return;
+  const int o = kSub * sub;
+  float x[kSub];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = e0 + tid + 64 * u, i = e / kLuNB, k = e - i * kLuNB;
-        v[u] = (i < nc && k < nc) ? A[(size_t)(j0 + i) * d + j0 + k] : 0.f;
+  for (int i = 0; i < kSub; ++i) {
+    const int fi = o + (low ? i : kSub - 1 - i);
+    float s = (i == n) ? 1.f : 0.f;
+#pragma unroll
+    for (int k = 0; k < i; ++k) s -= sm.L11[fi][o + (low ? k : kSub - 1 - k)] * x[k];
+    x[i] = low ? s : s / sm.L11[fi][fi];
+  }
+  float* out = a.dinv + (size_t)(2 * ((q0 + o) / kSub) + (low ? 0 : 1)) * (kSub * kSub);
+#pragma unroll
+  for (int i = 0; i < kSub; ++i) {
+    const int r = low ? i : kSub - 1 - i, c = low ? n : kSub - 1 - n;
+    out[r * kSub + c] = x[i];
+  }
+}
+
+// Columns s0 .. s0 + 31 (as far as they go): U12 = L11^{-1} A[pivots] of the
+// panel at column q0 = j0 - 32, written back, then A[active] -= L21 U12.  The
+// result stays in LDS (T[column][active row]) or goes back to memory.
+template <int NT, bool VEC, bool TO_LDS>
+__device__ __forceinline__ void update_columns(const LuArgs& a, int s0, float* T, PanelSmall& sm) {
+  constexpr int NW = NT / 64, TLD = NT + 4;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int d = a.d, q0 = a.j0 - kNB, R = d - a.j0, nc = min(kNB, d - s0);
+  const int g = lane >> 4, l16 = lane & 15;
+  if (tid < kNB) sm.prow[tid] = a.piv[q0 + tid];
+  // The wave's rows: 16-row blocks w, w + NW, ...; rows and columns past the
+  // end are read at a clamped place and never stored.
+  int crow[kRB][4], lrow[kRB];
+#pragma unroll
+  for (int t = 0; t < kRB; ++t) {
+    const int b = kSub * (w + NW * t);
+    lrow[t] = a.act[min(b + l16, R - 1)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) crow[t][r] = a.act[min(b + 4 * g + r, R - 1)];
+  }
+  __syncthreads();
+  // L11 and the slab's pivot rows: thread (i, c) of 32 x 32 (NT >= 256)
+  {
+    const int c = tid & 31;
+    for (int i = tid >> 5; i < kNB; i += NT / 32) {
+      const float* row = a.A + (size_t)sm.prow[i] * d;
+      const float lv = row[q0 + c], uv = row[s0 + min(c, nc - 1)];
+      sm.L11[i][c] = lv;
+      sm.U12T[c][i] = uv;
+    }
+  }
+  // The update's operands are requested before the substitution and used after
+  // it, except by 1024 threads, whose 128 registers do not hold them so long.
+  floatx4 fl[kRB][2], acc[kRB][2];
+  auto operands = [&](int t) {
+    if (kSub * (w + NW * t) >= R) return;
+    const float* lp = a.A + (size_t)lrow[t] * d + q0 + 4 * g;
+    fl[t][0] = load4<VEC>(lp);
+    fl[t][1] = load4<VEC>(lp + 16);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* cp = a.A + (size_t)crow[t][r] * d + s0;
+      acc[t][0][r] = cp[min(l16, nc - 1)];
+      acc[t][1][r] = cp[min(16 + l16, nc - 1)];
+    }
+  };
+  if (NT < 1024)
+#pragma unroll
+    for (int t = 0; t < kRB; ++t) operands(t);
+  __syncthreads();
+  if (tid < kNB) {  // a column per lane
+    float x[kNB];
+#pragma unroll
+    for (int i = 0; i < kNB; i += 4) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(&sm.U12T[tid][i]);
+      x[i] = v[0]; x[i + 1] = v[1]; x[i + 2] = v[2]; x[i + 3] = v[3];
+    }
+#pragma unroll
+    for (int i = 1; i < kNB; ++i) {
+      float s0v = x[i], s1v = 0.f;
+#pragma unroll
+      for (int k = 0; k < i; k += 4) {
+        const floatx4 l = *reinterpret_cast<const floatx4*>(&sm.L11[i][k]);
+        s0v -= l[0] * x[k];
+        if (k + 1 < i) s1v -= l[1] * x[k + 1];
+        if (k + 2 < i) s0v -= l[2] * x[k + 2];
+        if (k + 3 < i) s1v -= l[3] * x[k + 3];
       }
+      x[i] = s0v + s1v;
+    }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = e0 + tid + 64 * u, i = e / kLuNB, k = e - i * kLuNB;
-        Ls[i][k] = v[u];
+    for (int i = 0; i < kNB; i += 4)
+      *reinterpret_cast<floatx4*>(&sm.U12T[tid][i]) = floatx4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+  }
+  __syncthreads();
+  {
+    const int c = tid & 31;
+    if (c < nc)
+      for (int i = tid >> 5; i < kNB; i += NT / 32)
+        a.A[(size_t)sm.prow[i] * d + s0 + c] = sm.U12T[c][i];
+  }
+  if (NT == 1024)
+#pragma unroll
+    for (int t = 0; t < kRB; ++t) operands(t);
+  floatx4 fu[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      fu[h][s] = -*reinterpret_cast<const floatx4*>(&sm.U12T[16 * h + l16][16 * s + 4 * g]);
+#pragma unroll
+  for (int t = 0; t < kRB; ++t) {
+    const int b = kSub * (w + NW * t);
+    if (b >= R) continue;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          acc[t][h] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(fl[t][s][q], fu[h][s][q], acc[t][h], 0, 0, 0);
+    if (TO_LDS) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *reinterpret_cast<floatx4*>(T + (16 * h + l16) * TLD + b + 4 * g) = acc[t][h];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (b + 4 * g + r >= R) continue;
+        float* cp = a.A + (size_t)crow[t][r] * d + s0;
+        if (l16 < nc) cp[l16] = acc[t][0][r];
+        if (16 + l16 < nc) cp[16 + l16] = acc[t][1][r];
       }
     }
   }
-  __syncthreads();
-  const int n = s_n;
-  if (perm_block) {
-    if (tid < n) Sp[tid] = perm[s_rows[tid]];
-    __syncthreads();
-    if (tid == 0)
-      for (int k = 0; k < nc; ++k) {
-        const int sk = s_slot[k];
-        const int t = Sp[k];
-        Sp[k] = Sp[sk];
-        Sp[sk] = t;
+}
+
+// Links c0 .. c0 + 7 of a panel whose rows have W columns left (a[0 .. W), the
+// column of the link in a[0]).
+template <int NT, int W>
+__device__ __forceinline__ void panel_links(float (&x)[kNB], int c0, int nc, bool& active,
+                                            int& step, int row, const LuArgs& a, float* T,
+                                            PanelSmall& sm) {
+  constexpr int NW = NT / 64, TLD = NT + 4;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int s = 0; s < 8; ++s) {
+    const int c = c0 + s, par = s & 1;
+    if (c >= nc) return;
+    // |a| as an integer orders like |a| (a NaN above infinity); 0: not active
+    const unsigned key = active ? (__float_as_uint(x[0]) & 0x7fffffffu) + 1u : 0u;
+    const unsigned wm = wave_max(key);
+    const int src = __ffsll((unsigned long long)__ballot(key == wm)) - 1;
+    if (lane == src) {
+#pragma unroll
+      for (int i = 0; i < W; i += 4)
+        *reinterpret_cast<floatx4*>(&sm.slot[par][w][i]) =
+            floatx4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+      sm.skey[par][w] = wm;
+    }
+    lds_barrier();
+    // the first wave with the largest key: ties go to the lower row
+    const unsigned k = sm.skey[par][lane & (NW - 1)];
+    const unsigned km = (unsigned)__builtin_amdgcn_readfirstlane((int)row_max16(k));
+    const int ww = __ffsll((unsigned long long)__ballot(k == km)) - 1;
+    float p[W];
+#pragma unroll
+    for (int i = 0; i < W; i += 4) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(&sm.slot[par][ww][i]);
+      p[i] = v[0]; p[i + 1] = v[1]; p[i + 2] = v[2]; p[i + 3] = v[3];
+    }
+    const float prc = 1.f / p[0];
+    if (w == ww && lane == src) {
+      active = false;
+      step = c;
+    }
+    const float l = active ? x[0] * prc : 0.f;
+    T[c * TLD + tid] = l;
+#pragma unroll
+    for (int i = 0; i + 1 < W; ++i) x[i] = x[i + 1] - l * p[i + 1];
+    if (w == ww) {
+      // the row of R, as published; its multipliers are in T
+      const int pr = __builtin_amdgcn_readlane(row, src);
+      if (lane < W && c + lane < nc)
+        a.A[(size_t)pr * a.d + a.j0 + c + lane] = sm.slot[par][ww][lane];
+      if (lane == 0) {
+        a.piv[a.j0 + c] = pr;
+        if (!(fabsf(p[0]) > 0.f) || !isfinite(p[0])) atomicCAS(a.flags + F_ERR, 0, LST_ESINGULAR);
       }
-    __syncthreads();
-    if (tid < n) perm[s_rows[tid]] = Sp[tid];
+    }
+  }
+}
+
+template <int NT, bool VEC>
+__global__ __launch_bounds__(NT) void lu_panel_kernel(LuArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  constexpr int NW = NT / 64, TLD = NT + 4;
+  float* T = reinterpret_cast<float*>(lds_raw);
+  PanelSmall& sm = *reinterpret_cast<PanelSmall*>(lds_raw + (size_t)kNB * TLD * sizeof(float));
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int d = a.d, R = d - a.j0, nc = min(kNB, R);
+  if (blockIdx.x > 0) {
+    const int s0 = a.j0 + kNB * (int)blockIdx.x;
+    if (s0 < d)
+      update_columns<NT, VEC, false>(a, s0, T, sm);
+    else if (w == 0)
+      diag_inverses(a, a.j0 - kNB, sm);
     return;
   }
-  if (col >= d || (col >= j0 && col < j0 + nc)) return;
-  {
-    float v[2 * kLuNB];
-#pragma unroll
-    for (int u = 0; u < 2 * kLuNB; ++u) v[u] = u < n ? A[(size_t)s_rows[u] * d + col] : 0.f;
-#pragma unroll
-    for (int u = 0; u < 2 * kLuNB; ++u) S[u][tid] = v[u];
-  }
-  for (int k = 0; k < nc; ++k) {
-    const int sk = s_slot[k];
-    if (sk != k) {
-      const float t = S[k][tid];
-      S[k][tid] = S[sk][tid];
-      S[sk][tid] = t;
-    }
-  }
-  float x[kLuNB];
-#pragma unroll
-  for (int i = 0; i < kLuNB; ++i) x[i] = S[i][tid];
-  if (col >= j0 + nc) {
-#pragma unroll
-    for (int i = 1; i < kLuNB; ++i) {
-      float v = x[i];
-#pragma unroll
-      for (int k = 0; k < i; ++k) v -= Ls[i][k] * x[k];
-      x[i] = v;
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < 2 * kLuNB; ++u)
-    if (u < n) A[(size_t)s_rows[u] * d + col] = u < kLuNB ? x[u] : S[u][tid];
-}
-
-__global__ __launch_bounds__(256) void lu_iota_kernel(int* perm, int d) {
-  for (int j = blockIdx.x * 256 + threadIdx.x; j < d; j += gridDim.x * 256) perm[j] = j;
-}
-
-// One column block J0 .. J0 + nb of the row solves for rows r0 .. r0 + 15.
-// FWD: y = L^{-1} (P h), the right-hand side gathered from H through perm;
-// otherwise z = R^{-1} y, written to X2 and, scaled by -lr a_i, to Xout.
-template <bool FWD>
-__global__ __launch_bounds__(256) void lu_rows_kernel(const float* F, int d, int J0,
-                                                      const int* perm, const float* H, int m,
-                                                      float* X2, float* Xout, const float* acoef,
-                                                      float lr) {
-  __shared__ float Xs[kSolveRows][kSolveNB + 1];
-  __shared__ float Fs[kSolveNB][kSolveNB + 1];
-  __shared__ float Z[kSolveRows][kSolveNB + 1];
-  const int tid = threadIdx.x, r0 = blockIdx.x * kSolveRows;
-  const int nb = min(kSolveNB, d - J0);
-  const int rr = tid >> 4, q = tid & 15, i4 = q * 4;
-  const int row = r0 + rr;
-  // the right-hand side first (its loads overlap the product's)
-  float rhs[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int i = i4 + c;
-    rhs[c] = 0.f;
-    if (row < m && i < nb)
-      rhs[c] = FWD ? H[(size_t)row * d + perm[J0 + i]] : X2[(size_t)row * d + J0 + i];
-  }
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  const int kbeg = FWD ? 0 : J0 + nb, kend = FWD ? J0 : d;
-  // operands: thread t loads column t & 63 of rows (t >> 6) + 4 u
-  const int lc = tid & 63, lr4 = tid >> 6;
-  for (int k0 = kbeg; k0 < kend; k0 += kSolveNB) {
-    const int kn = min(kSolveNB, kend - k0);
-    float xv[kSolveRows / 4], fv[kSolveNB / 4];
-#pragma unroll
-    for (int u = 0; u < kSolveRows / 4; ++u) {
-      const int ro = lr4 + 4 * u;
-      xv[u] = (r0 + ro < m && lc < kn) ? X2[(size_t)(r0 + ro) * d + k0 + lc] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < kSolveNB / 4; ++u) {
-      const int i = lr4 + 4 * u;
-      fv[u] = (i < nb && lc < kn) ? F[(size_t)(J0 + i) * d + k0 + lc] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < kSolveRows / 4; ++u) Xs[lr4 + 4 * u][lc] = xv[u];
-#pragma unroll
-    for (int u = 0; u < kSolveNB / 4; ++u) Fs[lr4 + 4 * u][lc] = fv[u];
+  float x[kNB];
+  bool active = tid < R;
+  const int row = a.act[min(tid, R - 1)];
+  if (a.j0 > 0) {
+    update_columns<NT, VEC, true>(a, a.j0, T, sm);
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < kSolveNB; ++kk) {
-      const float x = Xs[rr][kk];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[c] += x * Fs[i4 + c][kk];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) Z[rr][i4 + c] = rhs[c] - acc[c];
-  // the diagonal block of F
-  {
-    float fv[kSolveNB / 4];
-#pragma unroll
-    for (int u = 0; u < kSolveNB / 4; ++u) {
-      const int i = lr4 + 4 * u;
-      fv[u] = (i < nb && lc < nb) ? F[(size_t)(J0 + i) * d + J0 + lc] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < kSolveNB / 4; ++u) Fs[lr4 + 4 * u][lc] = fv[u];
-  }
-  __syncthreads();
-  // row rr by its 16 lanes (one quarter of a wave): each entry waits for the
-  // entries before it (after it, going back), written by lane q == 0 of the
-  // same wave; the LDS accesses of a wave complete in order
-  if (FWD) {
-    for (int i = 0; i < nb; ++i) {
-      float s = 0.f;
-      for (int k = q; k < i; k += 16) s += Fs[i][k] * Z[rr][k];
-      s += __shfl_xor(s, 8);
-      s += __shfl_xor(s, 4);
-      s += __shfl_xor(s, 2);
-      s += __shfl_xor(s, 1);
-      if (q == 0) Z[rr][i] -= s;
-      asm volatile("" ::: "memory");
-    }
+    for (int c = 0; c < kNB; ++c) x[c] = T[c * TLD + tid];
   } else {
-    for (int i = nb - 1; i >= 0; --i) {
-      float s = 0.f;
-      for (int k = i + 1 + q; k < nb; k += 16) s += Fs[i][k] * Z[rr][k];
-      s += __shfl_xor(s, 8);
-      s += __shfl_xor(s, 4);
-      s += __shfl_xor(s, 2);
-      s += __shfl_xor(s, 1);
-      if (q == 0) Z[rr][i] = (Z[rr][i] - s) / Fs[i][i];
-      asm volatile("" ::: "memory");
+    const float* rp = a.A + (size_t)row * d;
+#pragma unroll
+    for (int c = 0; c < kNB; ++c) x[c] = rp[min(c, nc - 1)];
+  }
+  // (threads past the rows and columns past the panel hold values that are
+  // never used: a row that is not active takes no part, a column past the end
+  // is not reached)
+  int step = kNB;  // the link that chose this row
+  // a wave writes T only at its own rows, which only it has read
+  panel_links<NT, 32>(x, 0, nc, active, step, row, a, T, sm);
+  panel_links<NT, 24>(x, 8, nc, active, step, row, a, T, sm);
+  panel_links<NT, 16>(x, 16, nc, active, step, row, a, T, sm);
+  panel_links<NT, 8>(x, 24, nc, active, step, row, a, T, sm);
+  // the multipliers go back: 32 lanes a row, each up to the link that chose it
+  for (int r0 = 0; r0 < 64; r0 += 2) {
+    const int src = r0 + (lane >> 5), c = lane & 31;
+    const int rr = __shfl(row, src), st = __shfl(step, src);
+    const int t = 64 * w + src;
+    if (t < R && c < nc && c < st) a.A[(size_t)rr * d + a.j0 + c] = T[c * TLD + t];
+  }
+  // the rows that stay active, in order
+  const unsigned long long on = __ballot(active);
+  if (lane == 0) sm.wcnt[w] = __popcll(on);
+  __syncthreads();
+  int off = __popcll(on & ((1ull << lane) - 1ull));
+  for (int v = 0; v < w; ++v) off += sm.wcnt[v];
+  if (active) a.act_next[off] = row;
+  if (R <= kNB && w == 0) diag_inverses(a, a.j0, sm);  // the last panel (in the wave that wrote it)
+}
+
+__global__ __launch_bounds__(256) void lu_iota_kernel(int* act, int d) {
+  for (int j = blockIdx.x * 256 + threadIdx.x; j < d; j += gridDim.x * 256) act[j] = j;
+}
+
+// X_i = -lr a_i z_i with P A = L R and A z_i = h_i, 16 examples a workgroup.
+// Wave w owns the 16-blocks w, w + NW, ... of the unknowns (RB of them); the
+// accumulator of a block holds unknowns 4 g + r (g = lane / 16) of example
+// lane % 16.
+template <int RB, bool VEC>
+__global__ __launch_bounds__(1024) void lu_rows_kernel(const float* __restrict__ F,
+                                                       const int* __restrict__ piv,
+                                                       const float* __restrict__ dinv, int d,
+                                                       const float* __restrict__ H, int m,
+                                                       float* __restrict__ Xout,
+                                                       const float* __restrict__ acoef, float lr) {
+  constexpr int NW = 16;
+  constexpr int PF = RB <= 2 ? 4 : 2;  // links whose fragments are in flight
+  __shared__ floatx4 xs[2][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, l16 = lane & 15;
+  const int nb = (d + kSub - 1) / kSub;
+  const int ex = blockIdx.x * kSub + l16;
+  const float* hr = H + (size_t)min(ex, m - 1) * d;
+  floatx4 acc[RB];
+  const float* rp[RB];
+#pragma unroll
+  for (int t = 0; t < RB; ++t) {
+    const int b = kSub * (w + NW * t);
+    rp[t] = F + (size_t)piv[min(b + l16, d - 1)] * d;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = b + 4 * g + r;
+      const float h = hr[piv[min(j, d - 1)]];
+      acc[t][r] = j < d ? h : 0.f;
     }
   }
-  __syncthreads();
-  if (row < m) {
-    const float sc = FWD ? 0.f : -lr * acoef[row];
+  // Block J's columns of the rows of slot t.  Past the matrix's end they are
+  // read at a clamped place: unknowns past it are published as zeros, and
+  // accumulators of rows past it reach nothing else.  No branch, so that the
+  // loads of several links stay in flight.
+  auto frag = [&](int t, int J) {
+    const int k = kSub * J + 4 * g;
+    if (VEC) return *reinterpret_cast<const floatx4*>(rp[t] + min(k, d - 4));
+    return floatx4{rp[t][min(k, d - 1)], rp[t][min(k + 1, d - 1)], rp[t][min(k + 2, d - 1)],
+                   rp[t][min(k + 3, d - 1)]};
+  };
+  auto diag = [&](int J, int up) {
+    return *reinterpret_cast<const floatx4*>(dinv + (size_t)(2 * min(J, nb - 1) + up) *
+                                                        (kSub * kSub) +
+                                             l16 * kSub + 4 * g);
+  };
+  floatx4 dv[RB];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int i = i4 + c;
-      if (i < nb) {
-        const float z = Z[rr][i];
-        X2[(size_t)row * d + J0 + i] = z;
-        if (!FWD) Xout[(size_t)row * d + J0 + i] = sc * z;
+  for (int pass = 0; pass < 2; ++pass) {
+    const bool up = pass == 1;
+#pragma unroll
+    for (int t = 0; t < RB; ++t) dv[t] = diag(w + NW * t, pass);
+    // links in order of slots: while slot S is solved, the slots after it (up:
+    // before it) take every block, slot S the blocks before (after) its own
+#pragma unroll
+    for (int SS = 0; SS < RB; ++SS) {
+      const int S = up ? RB - 1 - SS : SS;
+      floatx4 f[PF][RB];
+      auto block_of = [&](int i) { return NW * S + (up ? NW - 1 - i : i); };
+      auto load = [&](floatx4(&fr)[RB], int i) {
+        const int J = block_of(min(i, NW - 1));
+#pragma unroll
+        for (int t = 0; t < RB; ++t)
+          if (up ? t <= S : t >= S) fr[t] = frag(t, min(J, nb - 1));
+      };
+#pragma unroll
+      for (int i = 0; i + 1 < PF; ++i) load(f[i], i);
+#pragma unroll 1
+      for (int i0 = 0; i0 < NW; i0 += PF) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+          const int i = i0 + u, J = block_of(i), par = u & 1;
+          load(f[(u + PF - 1) % PF], i + PF - 1);
+          if (J < nb) {  // uniform
+            const bool own = w == J - NW * S;
+            if (own) {
+              floatx4 xv = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                xv = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[S][q], acc[S][q], xv, 0, 0, 0);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) xv[r] = kSub * J + 4 * g + r < d ? xv[r] : 0.f;
+              acc[S] = xv;
+              xs[par][lane] = xv;
+            }
+            lds_barrier();
+            const floatx4 xb = -xs[par][lane];
+#pragma unroll
+            for (int tt = 0; tt < RB; ++tt) {
+              const int t = up ? RB - 1 - tt : tt;
+              const bool take = t == S ? (up ? w < J - NW * S : w > J - NW * S)
+                                       : (up ? t < S : t > S);
+              if (take) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                  acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u][t][q], xb[q], acc[t], 0, 0, 0);
+              }
+            }
+          }
+        }
       }
     }
   }
+  if (ex >= m) return;
+  const float sc = -lr * acoef[ex];
+  float* out = Xout + (size_t)ex * d;
+#pragma unroll
+  for (int t = 0; t < RB; ++t) {
+    const int j = kSub * (w + NW * t) + 4 * g;
+    if (VEC) {
+      if (j < d) *reinterpret_cast<floatx4*>(out + j) = acc[t] * sc;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (j + r < d) out[j + r] = acc[t][r] * sc;
+    }
+  }
+}
+
+template <int NT>
+hipError_t panel_launch(const LuArgs& a, int blocks, bool vec, hipStream_t s) {
+  const size_t lds = panel_lds_bytes(NT);
+  if (vec)
+    hipLaunchKernelGGL((lu_panel_kernel<NT, true>), dim3(blocks), dim3(NT), lds, s, a);
+  else
+    hipLaunchKernelGGL((lu_panel_kernel<NT, false>), dim3(blocks), dim3(NT), lds, s, a);
+  return hipGetLastError();
+}
+
+template <int NT>
+hipError_t panel_configure() {
+  const void* k[2] = {reinterpret_cast<const void*>(&lu_panel_kernel<NT, true>),
+                      reinterpret_cast<const void*>(&lu_panel_kernel<NT, false>)};
+  for (const void* f : k) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)panel_lds_bytes(NT));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int RB>
+hipError_t rows_launch(const float* F, const int* piv, const float* dinv, int d, const float* H,
+                       int m, float* Xout, const float* acoef, float lr, bool vec, hipStream_t s) {
+  const dim3 grid((m + kSub - 1) / kSub);
+  if (vec)
+    hipLaunchKernelGGL((lu_rows_kernel<RB, true>), grid, dim3(1024), 0, s, F, piv, dinv, d, H, m,
+                       Xout, acoef, lr);
+  else
+    hipLaunchKernelGGL((lu_rows_kernel<RB, false>), grid, dim3(1024), 0, s, F, piv, dinv, d, H, m,
+                       Xout, acoef, lr);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t lu_factor(float* A, int d, int* ipiv, int* perm, int* flags, hipStream_t s) {
+size_t lu_dinv_floats(int d) { return (size_t)2 * ((d + kNB - 1) / kNB * 2) * kSub * kSub; }
+
+hipError_t lu_configure() {
+  hipError_t e = panel_configure<256>();
+  if (e == hipSuccess) e = panel_configure<512>();
+  if (e == hipSuccess) e = panel_configure<1024>();
+  return e;
+}
+
+hipError_t lu_factor(float* A, int d, int* piv, int* act, float* dinv, int* flags,
+                     hipStream_t s) {
   if (d < 1 || d > kLuMaxD) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(lu_iota_kernel, dim3((d + 255) / 256), dim3(256), 0, s, perm, d);
-  // the trailing update runs as the GEMM task of a step launch (32 x 32 tiles)
-  StepCtx c{};
-  c.m = 1;
-  c.d = d;
-  for (int j0 = 0; j0 < d; j0 += kLuNB) {
-    hipLaunchKernelGGL(lu_panel_kernel, dim3(1), dim3(kPanelThreads), 0, s, A, d, j0, ipiv,
-                       flags);
-    hipLaunchKernelGGL(lu_apply_kernel, dim3((d + 63) / 64 + 1), dim3(64), 0, s, A, d, j0,
-                       (const int*)ipiv, perm);
-    const int nc = d - j0 < kLuNB ? d - j0 : kLuNB;
-    const int rest = d - j0 - nc;
-    if (rest > 0) {
-      StepLaunch L{};
-      L.lk = 2;
-      L.ntask = 1;
-      L.kind[0] = TK_GEMM;
-      L.gemm.np = 1;
-      L.gemm.p[0] = gemm_problem(L_NN, rest, rest, nc,
-                                 vmat(A + (size_t)(j0 + nc) * d + j0, d, rest),
-                                 vmat(A + (size_t)j0 * d + j0 + nc, d, nc),
-                                 A + (size_t)(j0 + nc) * d + j0 + nc, d, -1.f, 1.f, EPI_STORE);
-      L.gemm.p[0].tile = 32;
-      const hipError_t e = step_launch(c, L, 2, s);
-      if (e != hipSuccess) return e;
-    }
+  hipLaunchKernelGGL(lu_iota_kernel, dim3((d + 255) / 256), dim3(256), 0, s, act, d);
+  const bool vec = d % 4 == 0;  // A comes from the device allocator: its rows are then aligned
+  for (int j0 = 0, p = 0; j0 < d; j0 += kNB, ++p) {
+    const int R = d - j0;
+    const LuArgs a{A, d, j0, piv, act + (p & 1) * d, act + ((p & 1) ^ 1) * d, dinv, flags};
+    // the columns right of the panel, and the previous panel's diagonal blocks
+    const int blocks = j0 == 0 ? 1 : 1 + (R > kNB ? (R - kNB + kNB - 1) / kNB : 0) + 1;
+    // one active row per thread; fewer waves make the link's barrier shorter
+    const hipError_t e = R <= 256   ? panel_launch<256>(a, blocks, vec, s)
+                         : R <= 512 ? panel_launch<512>(a, blocks, vec, s)
+                                    : panel_launch<1024>(a, blocks, vec, s);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }
 
-hipError_t lu_solve_rows(const float* F, const int* perm, int d, const float* H, int m, float* X2,
-                         float* Xout, const float* acoef, float lr, hipStream_t s) {
+hipError_t lu_solve_rows(const float* F, const int* piv, const float* dinv, int d, const float* H,
+                         int m, float* Xout, const float* acoef, float lr, hipStream_t s) {
   if (d < 1 || d > kLuMaxD || m < 1) return hipErrorInvalidValue;
-  const dim3 grid((m + kSolveRows - 1) / kSolveRows);
-  for (int J0 = 0; J0 < d; J0 += kSolveNB)
-    hipLaunchKernelGGL(lu_rows_kernel<true>, grid, dim3(256), 0, s, F, d, J0, perm, H, m, X2,
-                       Xout, acoef, lr);
-  for (int J0 = (d - 1) / kSolveNB * kSolveNB; J0 >= 0; J0 -= kSolveNB)
-    hipLaunchKernelGGL(lu_rows_kernel<false>, grid, dim3(256), 0, s, F, d, J0, perm, H, m, X2,
-                       Xout, acoef, lr);
-  return hipGetLastError();
+  const bool vec = d % 4 == 0;  // F and Xout come from the device allocator
+  if (d <= 256) return rows_launch<1>(F, piv, dinv, d, H, m, Xout, acoef, lr, vec, s);
+  if (d <= 512) return rows_launch<2>(F, piv, dinv, d, H, m, Xout, acoef, lr, vec, s);
+  return rows_launch<4>(F, piv, dinv, d, H, m, Xout, acoef, lr, vec, s);
 }
 
 }  // namespace lst

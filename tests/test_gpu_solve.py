@@ -142,3 +142,43 @@ def test_step_solve_refuses_wide_state(gpu_lib):
     with pytest.raises(lst.LstError) as e:
         layer.step_solve(H, idx, val, 1e-3)
     assert e.value.code == lst.LST_EINVAL
+
+
+@pytest.mark.parametrize("d,m", [(1, 1), (2, 3), (16, 5), (31, 17), (32, 16), (33, 1), (64, 33),
+                                 (100, 40), (255, 15), (256, 130), (257, 31), (288, 16), (301, 77),
+                                 (511, 2), (512, 128), (513, 48), (775, 20), (1023, 17),
+                                 (1024, 100)])
+def test_step_solve_row_solutions(gpu_lib, d, m):
+    """Z = U_new^{-T} H itself, at the edges of panels (32), diagonal blocks (16), thread
+    counts (256, 512, 1024) and example blocks (16), for an orthogonal U whose factorisation
+    needs row interchanges at nearly every step.  With V = 0 and one target of its own per
+    example, V_new holds 2 lr y z_i in the target's row.  Bound: the backward error of
+    Gaussian elimination with partial pivoting, growth times d eps, with the d^(2/3) growth of
+    random matrices, and cond(U_new) < 2."""
+    import paper_1412_7091_amd as lst
+
+    rng = np.random.default_rng(1000 * d + m)
+    q, r = np.linalg.qr(rng.standard_normal((d, d)))
+    U = np.ascontiguousarray(q * np.sign(np.diag(r)), dtype=np.float32)
+    H = (rng.standard_normal((m, d)) / np.sqrt(d)).astype(np.float32)
+    # 2 lr ||H^T H|| <= 1/2
+    lr = np.float32(0.25 / max(1.0, np.linalg.norm(H.astype(np.float64), 2) ** 2))
+    D = m + 3
+    idx = rng.permutation(D)[:m].astype(np.int32).reshape(m, 1)
+    val = (1.0 + rng.random((m, 1))).astype(np.float32)
+    dev = torch.device("cuda:0")
+    layer = lst.FactoredOutputLayer(torch.zeros((D, d), device=dev), torch.from_numpy(U).to(dev),
+                                    m_max=m, K_max=1)
+    layer.step_solve(*(torch.from_numpy(x).to(dev) for x in (H, idx, val)), float(lr))
+    assert layer.sync() == 0
+    V = layer.get_V().cpu().numpy().astype(np.float64)
+    H64, U64 = H.astype(np.float64), U.astype(np.float64)
+    U_new = U64 - 2.0 * float(lr) * (U64 @ H64.T) @ H64
+    Z = np.linalg.solve(U_new.T, H64.T).T
+    want = np.zeros((D, d))
+    want[idx[:, 0]] = 2.0 * float(lr) * val.astype(np.float64) * Z
+    err = np.linalg.norm(V - want) / np.linalg.norm(want)
+    bound = 4.0 * d ** (2.0 / 3.0) * np.sqrt(d) * 2.0 ** -24 + 4.0 * 2.0 ** -24
+    print(f"d={d} m={m}: {err:.2e} (bound {bound:.2e})", flush=True)
+    assert err <= bound
+    layer.close()
