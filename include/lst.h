@@ -344,8 +344,8 @@ typedef struct lst_input lst_input;
 
 /*
  * lst_input_init -- create an input layer; W_in (device, D_in x d) is copied.
- * D_in >= 1, 1 <= d <= 4096.  Besides W_in the layer holds a 1.8 MB table of
- * the rows of one update.  Synchronous.
+ * D_in >= 1, 1 <= d <= 4096.  Besides W_in the layer holds about 2.5 MB
+ * + 2 KB d of workspace for the rows of one update.  Synchronous.
  */
 int lst_input_init(lst_input** out, int64_t D_in, int32_t d, const float* W_in,
                    void* hip_stream);
@@ -364,9 +364,9 @@ int lst_input_forward(lst_input* s, int32_t m, int32_t K, const int32_t* idx, co
 /*
  * lst_input_update -- W_in <- W_in - lr X^T grad_A (section 2.2: W_in[u_k] -=
  * lr v_k grad_a for every pair of every example; pairs that share a row add
- * up, in (example, pair) order, and each row is written once; a row named by
- * 64 or more pairs is summed in that order over each sixteenth of the m K
- * pairs, the sixteen sums then added in order).  grad_A
+ * up, in (example, pair) order, and each row is written once; the pairs of a
+ * row named by 64 or more are summed in that order in groups of 64, and
+ * the groups' sums added in order (four to a part, then the parts)).  grad_A
  * (device, m x d) is dL/dA.  lr > 0 and finite.  Rows no pair refers to are
  * not touched.  Skipped entirely (W_in unchanged) while the sticky status is
  * set, e.g. by an index outside [-1, D_in) in this call.

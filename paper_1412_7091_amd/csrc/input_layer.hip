@@ -4,17 +4,35 @@
 //   forward: A[i, :] = sum_k v_ik W_in[u_ik, :]           (O(K d) per example)
 //   update:  W_in[r, :] -= lr * sum_{(i,k): u_ik = r} v_ik dA[i, :]
 // touch only the rows the minibatch refers to.  The update writes each row
-// once, from the wave of the row's first slot (in (example, pair) order),
-// which adds the contributions of all its slots in that order: deterministic,
-// with no atomics on W_in.  A hash table (row -> first slot, number of slots)
-// built by a pass over the slots finds the owner of a row in O(1); a row held
-// by one slot is updated at once, a repeated row's owner scans the later slots
-// until it has met them all, and a row held by kInputHotSlots slots or more is
-// summed by a block of sixteen waves (fixed sixteenths of the slots, their sums
-// added in order).
+// once and adds its pairs in (example, pair) order (long lists in fixed parts):
+// deterministic, with no atomics on W_in.  A slot is a pair's position i K + k.
+//
+// Up to kInputSmall slots the update is one launch, a wave per slot: every
+// wave reads all the indices (8 KB at most, in flight together) and so checks
+// them, and finds its row's slots and whether it is the first, without any
+// table.  Larger calls are grouped first (four launches):
+//   group   blocks of 1024 slots sort theirs by (row, slot) in LDS; the first
+//           slot of each run counts the run in an open-addressing table of the
+//           rows: atomics per block and row, however often the block names it;
+//   update  rows that one block names: the wave of the run sums its slots.  Rows
+//           that several blocks name are listed as their second run arrives and
+//           taken in turn by other waves, whose lane b looks for block b's run
+//           (they are the frequent rows, next to each other in sorted order).
+//           Whoever updates a row empties its table entry, so the table needs
+//           no pass of its own;
+//   hot     rows of kInputHotSlots slots or more: a block per kPartSlots slots of
+//           the row, 64 to a wave; the sums of rows of several parts are added
+//           in part order by one more launch.
+// Measured at d = 512, m K = 65 536, Zipf 1.1 (the four launches): 15 + 23 + 13
+// + 5 us; uniform rows, update and forward pass together, 126 us (670 before).
+// The table of slots that this replaces took one atomic per slot, 8600 of them
+// at the most frequent row (178 us), and the owner of a repeated row read the
+// later indices to find its slots (398 us), hot rows another 126 us.  m K =
+// 1280, d = 500: 6.3 us (four launches, 21 us).
 #include <math.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <new>
 
 #include "lst_internal.h"
@@ -26,29 +44,28 @@ struct lst_input {
   hipStream_t stream = nullptr;
   float* W = nullptr;
   int* flags = nullptr;  // [0]: sticky status
-  // open-addressing table of the rows of one update (empty between calls):
-  // key (-1 empty), smallest slot, number of slots; and, per slot, the table
-  // entry it owns (-1 if none), from which the table is emptied
-  int* hkey = nullptr;
-  int* hmin = nullptr;
-  int* hcnt = nullptr;
-  int* own = nullptr;
-  // rows held by at least kInputHotSlots slots, summed by input_hot_kernel
-  // ([0]: count, then the rows)
-  int* hot = nullptr;
+  // open-addressing table of the rows of one large update (empty between
+  // calls): row in the upper, number of runs in the lower 32 bits
+  unsigned long long* table = nullptr;
+  // per sorted position: row, pair (offset of the example's row of dA, value),
+  // length of the run that starts there (0: none does) and the run's table
+  // entry
+  int* srow = nullptr;
+  uint2* spair = nullptr;
+  int* rlen = nullptr;
+  int* rent = nullptr;
+  int* piv = nullptr;    // the last row of each 64 positions, then of each 16
+  int* multi = nullptr;  // table entries of the rows several blocks name ([0]: count)
+  // parts of the rows of at least kInputHotSlots slots: [0] = (parts, rows of
+  // several parts, sums taken of psum), then (row, part, slots of the row, the
+  // row's first sum in psum); the rows of several parts; and the sums
+  int4* part = nullptr;
+  int4* split = nullptr;
+  float* psum = nullptr;
 };
 
 namespace lst {
 namespace {
-
-// Every index in [-1, D); otherwise the sticky status becomes LST_EINDEX.
-__global__ void input_validate_kernel(const int32_t* __restrict__ idx, int n, int64_t D,
-                                      int* flags) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const int r = idx[e];
-  if (r < -1 || (int64_t)r >= D) atomicCAS(flags, 0, LST_EINDEX);
-}
 
 // Slots (and table entries) of the row table: twice the largest number of
 // slots, so that the table is at most half full.
@@ -56,146 +73,136 @@ constexpr int kInputMaxSlots = 65536;
 constexpr int kInputHashBits = 17;
 constexpr int kInputHashSize = 1 << kInputHashBits;
 static_assert(kInputHashSize >= 2 * kInputMaxSlots, "the row table must stay half empty");
-// A row held by this many slots or more is summed by a block of 16 waves, each
-// over a fixed sixteenth of the slots (the partial sums then added in order).
+// Slots up to which the update is one launch: each wave then reads 8 KB of
+// indices, and a row that every slot names (the worst case) takes 55 us, as much
+// as the grouped form; at 2000 slots of a Zipf 1.1 input the one launch takes
+// 14 us, the grouped form 35.
+constexpr int kInputSmall = 2048;
+constexpr int kSortBlock = 1024;       // slots sorted by one block
+static_assert(kInputMaxSlots / kSortBlock <= 64, "a lane of a wave per sorted block");
+// Rows of this many slots or more are not left to one wave.
 constexpr int kInputHotSlots = 64;
-constexpr int kInputMaxHot = kInputMaxSlots / kInputHotSlots;
+constexpr int kPartSlots = 256;  // slots of a hot row that one block sums
+constexpr int kMaxParts = kInputMaxSlots / kInputHotSlots + kInputMaxSlots / kPartSlots;
+constexpr int kMaxSplit = kInputMaxSlots / kPartSlots;     // rows of several parts
+constexpr int kMaxSums = 2 * kInputMaxSlots / kPartSlots;  // their parts
 
 __device__ __forceinline__ unsigned input_hash(int r) {
   return ((unsigned)r * 2654435761u) >> (32 - kInputHashBits);
 }
 
-// Validates slot e's index and enters its row into the table: the entry keeps
-// the smallest slot holding the row and the number of slots holding it.
-__global__ void input_insert_kernel(const int32_t* __restrict__ idx, int n, int64_t D,
-                                    int* hkey, int* hmin, int* hcnt, int* flags) {
+// An empty table entry (no row is 0x7fffffff or above).
+constexpr unsigned long long kNoEntry = ~0ull;
+
+__global__ void input_table_init_kernel(unsigned long long* table, int* multi) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const int r = idx[e];
-  if (r < -1 || (int64_t)r >= D) {
-    atomicCAS(flags, 0, LST_EINDEX);
-    return;
-  }
-  if (r < 0) return;
-  unsigned h = input_hash(r);
-  for (int probe = 0; probe < kInputHashSize; ++probe) {
-    const int prev = atomicCAS(hkey + h, -1, r);
-    if (prev == -1 || prev == r) {
-      atomicMin(hmin + h, e);
-      atomicAdd(hcnt + h, 1);
-      return;
-    }
-    h = (h + 1) & (kInputHashSize - 1);
-  }
+  if (e == 0) multi[0] = 0;
+  if (e < kInputHashSize) table[e] = kNoEntry;
 }
 
-// Empties the entries recorded in own[] (one per distinct row) and the list
-// of hot rows.
-__global__ void input_clear_kernel(int* own, int n, int* hkey, int* hmin, int* hcnt, int* hot) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e == 0) hot[0] = 0;
-  if (e >= n) return;
-  const int h = own[e];
-  if (h < 0) return;
-  hkey[h] = -1;
-  hmin[h] = 0x7fffffff;
-  hcnt[h] = 0;
-  own[e] = -1;
+// The wave's number in its block, in a scalar register: what depends on it
+// alone (an example's pairs) is then loaded once per wave.
+__device__ __forceinline__ int wave_index() {
+  return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
-// The empty table (init): every key -1, every smallest slot INT_MAX, counts 0.
-__global__ void input_table_init_kernel(int* hkey, int* hmin, int* hcnt, int* own, int* hot) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e == 0) hot[0] = 0;
-  if (e < kInputHashSize) {
-    hkey[e] = -1;
-    hmin[e] = 0x7fffffff;
-    hcnt[e] = 0;
+// Four columns of a row from col on (16-byte access when VEC; columns past d
+// read as zero and are not written).
+template <bool VEC>
+__device__ __forceinline__ float4 row_load4(const float* row, int col, int d) {
+  float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (VEC) {
+    if (col < d) w = *reinterpret_cast<const float4*>(row + col);
+  } else {
+    if (col < d) w.x = row[col];
+    if (col + 1 < d) w.y = row[col + 1];
+    if (col + 2 < d) w.z = row[col + 2];
+    if (col + 3 < d) w.w = row[col + 3];
   }
-  if (e < kInputMaxSlots) own[e] = -1;
+  return w;
+}
+template <bool VEC>
+__device__ __forceinline__ void row_store4(float* row, int col, int d, float4 w) {
+  if (VEC) {
+    if (col < d) *reinterpret_cast<float4*>(row + col) = w;
+  } else {
+    if (col < d) row[col] = w.x;
+    if (col + 1 < d) row[col + 1] = w.y;
+    if (col + 2 < d) row[col + 2] = w.z;
+    if (col + 3 < d) row[col + 3] = w.w;
+  }
+}
+__device__ __forceinline__ void add4(float4& a, float v, const float4& w) {
+  a.x += v * w.x; a.y += v * w.y; a.z += v * w.z; a.w += v * w.w;
 }
 
-// Pairs (or slots) handled per round: their loads are all issued before the
-// first result is used, so a long list pays the memory latency once per round.
-constexpr int kInputBatch = 8;
-// Slots whose rows of dA an owner wave has in flight at once.
-constexpr int kInputRows = 4;
+// Inputs of up to kInputSplitK pairs: a wave per (example, 256 columns), the
+// example's rows all in flight together, added in pair order, its indices checked
+// on the way (m = 128, K = 10, d = 500: 3.9 us; 11.0 and a 1.7 us launch for the
+// check with a wave per example and two rounds of rows).  Longer inputs: below.
+constexpr int kInputSplitK = 16;
 
-// A[i, :] = sum_k v_ik W[u_ik, :], one wave per example, pairs in order.
-// Columns in chunks of 256 (four per lane; 16-byte loads when VEC).
 template <bool VEC>
 __global__ __launch_bounds__(256) void input_forward_kernel(const float* __restrict__ W,
                                                             int64_t D, int d,
                                                             const int32_t* __restrict__ idx,
                                                             const float* __restrict__ val, int m,
-                                                            int K, float* __restrict__ A) {
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (i >= m) return;
+                                                            int K, float* __restrict__ A,
+                                                            int* flags) {
+  const int nch = (d + 255) / 256;
+  const int w = blockIdx.x * 4 + wave_index(), lane = threadIdx.x & 63;
+  if (w >= m * nch) return;
+  const int i = w / nch, col = (w - i * nch) * 256 + 4 * lane;
   const int32_t* ip = idx + (size_t)i * K;
   const float* vp = val + (size_t)i * K;
-  for (int c0 = 0; c0 < d; c0 += 256) {
-    const int col = c0 + 4 * lane;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    for (int k0 = 0; k0 < K; k0 += kInputBatch) {
-      float4 w[kInputBatch];
-      float v[kInputBatch];
+  int r[kInputSplitK];
+  float v[kInputSplitK];
 #pragma unroll
-      for (int u = 0; u < kInputBatch; ++u) {
-        const int k = k0 + u;
-        const int r = k < K ? ip[k] : -1;
-        // padding, a bad index (flagged elsewhere) and pairs past K add nothing
-        const bool on = r >= 0 && (int64_t)r < D;
-        v[u] = on ? vp[k] : 0.f;
-        const float* row = W + (size_t)(on ? r : 0) * d;
-        w[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (on && col < d) {
-          if (VEC) {
-            w[u] = *reinterpret_cast<const float4*>(row + col);
-          } else {
-            w[u].x = row[col];
-            if (col + 1 < d) w[u].y = row[col + 1];
-            if (col + 2 < d) w[u].z = row[col + 2];
-            if (col + 3 < d) w[u].w = row[col + 3];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kInputBatch; ++u) {
-        if (k0 + u >= K) break;
-        a0 += v[u] * w[u].x; a1 += v[u] * w[u].y; a2 += v[u] * w[u].z; a3 += v[u] * w[u].w;
-      }
-    }
-    float* out = A + (size_t)i * d;
-    if (VEC) {
-      if (col < d) *reinterpret_cast<float4*>(out + col) = make_float4(a0, a1, a2, a3);
-    } else {
-      if (col < d) out[col] = a0;
-      if (col + 1 < d) out[col + 1] = a1;
-      if (col + 2 < d) out[col + 2] = a2;
-      if (col + 3 < d) out[col + 3] = a3;
-    }
+  for (int u = 0; u < kInputSplitK; ++u) {
+    r[u] = ip[min(u, K - 1)];
+    v[u] = vp[min(u, K - 1)];
   }
+  float4 g[kInputSplitK];
+  bool bad = false;
+#pragma unroll
+  for (int u = 0; u < kInputSplitK; ++u) {
+    // padding, a bad index and pairs past K add nothing
+    const bool on = u < K && r[u] >= 0 && (int64_t)r[u] < D;
+    bad |= u < K && (r[u] < -1 || (int64_t)r[u] >= D);
+    if (!on) r[u] = -1;
+    g[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (on) g[u] = row_load4<VEC>(W + (size_t)r[u] * d, col, d);
+  }
+  if (bad && lane == 0) atomicCAS(flags, 0, LST_EINDEX);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int u = 0; u < kInputSplitK; ++u)
+    if (r[u] >= 0) add4(acc, v[u], g[u]);
+  row_store4<VEC>(A + (size_t)i * d, col, d, acc);
 }
+
+// Pairs handled per round by the longer inputs: their loads are all issued
+// before the first result is used.
+constexpr int kInputBatch = 8;
 
 // Long inputs (K > kInputSplitK): one block per (example, 256-column chunk);
 // wave w sums the pairs of the w-th quarter of the example's list in order,
 // and the four partial sums are added in wave order, so the result does not
 // depend on timing.
-constexpr int kInputSplitK = 16;
-
 template <bool VEC>
 __global__ __launch_bounds__(256) void input_forward_split_kernel(
     const float* __restrict__ W, int64_t D, int d, const int32_t* __restrict__ idx,
-    const float* __restrict__ val, int m, int K, float* __restrict__ A) {
+    const float* __restrict__ val, int m, int K, float* __restrict__ A, int* flags) {
   __shared__ float4 part[3][64];
   const int nch = (d + 255) / 256;
   const int i = blockIdx.x / nch, c0 = (blockIdx.x % nch) * 256;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_index(), lane = threadIdx.x & 63;
   const int col = c0 + 4 * lane;
   const int q = (K + 3) / 4, kb = wave * q, ke = min(K, kb + q);
   const int32_t* ip = idx + (size_t)i * K;
   const float* vp = val + (size_t)i * K;
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  bool bad = false;
   for (int k0 = kb; k0 < ke; k0 += kInputBatch) {
     float4 w[kInputBatch];
     float v[kInputBatch];
@@ -204,247 +211,551 @@ __global__ __launch_bounds__(256) void input_forward_split_kernel(
       const int k = k0 + u;
       const int r = k < ke ? ip[k] : -1;
       const bool on = r >= 0 && (int64_t)r < D;
+      bad |= r < -1 || (int64_t)r >= D;
       v[u] = on ? vp[k] : 0.f;
-      const float* row = W + (size_t)(on ? r : 0) * d;
       w[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (on && col < d) {
-        if (VEC) {
-          w[u] = *reinterpret_cast<const float4*>(row + col);
-        } else {
-          w[u].x = row[col];
-          if (col + 1 < d) w[u].y = row[col + 1];
-          if (col + 2 < d) w[u].z = row[col + 2];
-          if (col + 3 < d) w[u].w = row[col + 3];
-        }
-      }
+      if (on) w[u] = row_load4<VEC>(W + (size_t)r * d, col, d);
     }
 #pragma unroll
     for (int u = 0; u < kInputBatch; ++u) {
       if (k0 + u >= ke) break;
-      a0 += v[u] * w[u].x; a1 += v[u] * w[u].y; a2 += v[u] * w[u].z; a3 += v[u] * w[u].w;
+      add4(acc, v[u], w[u]);
     }
   }
-  if (wave > 0) part[wave - 1][lane] = make_float4(a0, a1, a2, a3);
+  if (bad && lane == 0) atomicCAS(flags, 0, LST_EINDEX);
+  if (wave > 0) part[wave - 1][lane] = acc;
   __syncthreads();
   if (wave != 0) return;
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     const float4 o = part[p][lane];
-    a0 += o.x; a1 += o.y; a2 += o.z; a3 += o.w;
+    acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
   }
-  float* out = A + (size_t)i * d;
-  if (VEC) {
-    if (col < d) *reinterpret_cast<float4*>(out + col) = make_float4(a0, a1, a2, a3);
-  } else {
-    if (col < d) out[col] = a0;
-    if (col + 1 < d) out[col + 1] = a1;
-    if (col + 2 < d) out[col + 2] = a2;
-    if (col + 3 < d) out[col + 3] = a3;
+  row_store4<VEC>(A + (size_t)i * d, col, d, acc);
+}
+
+// ------------------------------------------------------------------- update
+// Rows of dA in flight in a wave that sums a list, two 256-column chunks each.
+constexpr int kListRows = 8;
+// Loads in flight of a wave that sums 64 columns of a hot row (a row of 2048
+// slots: 52 us, with 32 loads 79).
+constexpr int kHotLoads = 64;
+
+// acc += sum over the list's slots t0 .. t0 + cnt - 1 (cnt <= 64; lane l holds
+// slot l's value v and the offset o of its row of dA) of v dA[row], in order,
+// columns cg + 256 c + 4 lane (c < 2).
+template <bool VEC>
+__device__ __forceinline__ void sum_list(const float* gA, int d, int cg, int cnt, float v,
+                                         unsigned o, float4 (&acc)[2]) {
+  const int lane = threadIdx.x & 63;
+  for (int t0 = 0; t0 < cnt; t0 += kListRows) {
+    float4 g[kListRows][2];
+#pragma unroll
+    for (int u = 0; u < kListRows; ++u) {
+      // slots past the list re-read its last row
+      const float* gr = gA + (unsigned)__builtin_amdgcn_readlane((int)o, min(t0 + u, cnt - 1));
+#pragma unroll
+      for (int c = 0; c < 2; ++c) g[u][c] = row_load4<VEC>(gr, cg + 256 * c + 4 * lane, d);
+    }
+#pragma unroll
+    for (int u = 0; u < kListRows; ++u) {
+      if (t0 + u >= cnt) break;
+      const float vu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), t0 + u));
+#pragma unroll
+      for (int c = 0; c < 2; ++c) add4(acc[c], vu, g[u][c]);
+    }
   }
 }
 
-// One wave per slot e = i*K + k.  The wave of the first slot holding row r
-// (from the table) records the entry it owns, then sums v dA over every slot
-// holding r, in slot order, and updates the row: at once when the row has one
-// slot, else scanning the later slots (kInputBatch chunks of 64 per round)
-// until it has met all of them.  With the sticky status set, ownership is still
-// recorded (the table must be emptied) but W is left alone.
-__global__ __launch_bounds__(256) void input_update_kernel(float* __restrict__ W, int64_t D,
-                                                           int d,
-                                                           const int32_t* __restrict__ idx,
-                                                           const float* __restrict__ val,
-                                                           const float* __restrict__ gA, int n,
-                                                           int K, float lr, const int* hkey,
-                                                           const int* hmin, const int* hcnt,
-                                                           int* own, int* hot, const int* flags) {
-  const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (e >= n) return;
-  const int r = idx[e];
-  if (r < 0 || (int64_t)r >= D) return;  // padding, or an index the insert pass flagged
-  unsigned h = input_hash(r);
-  int probe = 0;
-  while (probe < kInputHashSize && hkey[h] != r) {
-    h = (h + 1) & (kInputHashSize - 1);
-    ++probe;
+// The same for one column a lane (col; offset in bounds for every lane), cnt <=
+// 64: groups of kHotLoads are summed by themselves and then added.
+__device__ __forceinline__ float sum_list_col(const float* gA, int col, int cnt, float v,
+                                              unsigned o) {
+  float acc = 0.f;
+  for (int t0 = 0; t0 < cnt; t0 += kHotLoads) {
+    float g[kHotLoads];
+#pragma unroll
+    for (int u = 0; u < kHotLoads; ++u)
+      g[u] = gA[(unsigned)__builtin_amdgcn_readlane((int)o, min(t0 + u, cnt - 1)) + (unsigned)col];
+    float part = 0.f;
+#pragma unroll
+    for (int u = 0; u < kHotLoads; ++u) {
+      const float vu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), min(t0 + u, 63)));
+      if (t0 + u < cnt) part += vu * g[u];
+    }
+    acc += part;
   }
-  if (probe == kInputHashSize || hmin[h] != e) return;
-  if (lane == 0) own[e] = (int)h;
-  if (*flags) return;
-  const int cnt = hcnt[h];
-  if (cnt >= kInputHotSlots) {
-    if (lane == 0) hot[1 + atomicAdd(hot, 1)] = r;
+  return acc;
+}
+
+// Row r -= lr (sum over the wave's list of cnt slots, lane l holding v and o).
+template <bool VEC>
+__device__ __forceinline__ void update_row(float* W, const float* gA, int d, int r, int cnt,
+                                           float v, unsigned o, float lr) {
+  const int lane = threadIdx.x & 63;
+  float* row = W + (size_t)r * d;
+  for (int cg = 0; cg < d; cg += 512) {
+    float4 old[2], acc[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      old[c] = row_load4<VEC>(row, cg + 256 * c + 4 * lane, d);
+      acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    sum_list<VEC>(gA, d, cg, cnt, v, o, acc);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      old[c].x -= lr * acc[c].x; old[c].y -= lr * acc[c].y;
+      old[c].z -= lr * acc[c].z; old[c].w -= lr * acc[c].w;
+      row_store4<VEC>(row, cg + 256 * c + 4 * lane, d, old[c]);
+    }
+  }
+}
+
+// Up to 64 NU slots, a wave per slot.  Every wave holds all the indices, so
+// each finds any bad one (and then nothing is written).  The wave of a row's
+// first slot updates the row; a row of kInputHotSlots slots or more is shared
+// out by columns, 64 to each of its first waves (d <= 4096 = 64 x 64).
+template <int NU, bool VEC>
+__global__ __launch_bounds__(256) void input_update_small_kernel(
+    float* __restrict__ W, int64_t D, int d, const int32_t* __restrict__ idx,
+    const float* __restrict__ val, const float* __restrict__ gA, int n, int K, float lr,
+    int* flags) {
+  __shared__ unsigned short list[4][64 * NU];
+  const int w = wave_index(), lane = threadIdx.x & 63;
+  const int e = blockIdx.x * 4 + w;
+  if (e >= n) return;
+  int x[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) x[u] = idx[min(64 * u + lane, n - 1)];
+  const int r = idx[e];
+  const int pending = *flags;
+  bool bad = false;
+#pragma unroll
+  for (int u = 0; u < NU; ++u) bad |= x[u] < -1 || (int64_t)x[u] >= D;
+  if (__ballot(bad) != 0ull) {
+    if (lane == 0) atomicCAS(flags, 0, LST_EINDEX);
     return;
   }
-  const bool vec = (d % 4 == 0);
-  // columns in groups of 1024 (four 256-column chunks per lane); one scan per group
-  for (int cg = 0; cg < d; cg += 1024) {
-    float4 acc[4];
+  if (r < 0 || pending != 0) return;
+  int cnt = 0, first = n, before = 0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int nc = min(4, (d - cg + 255) / 256);  // chunks of this group
-    int met = 0;
-    for (int s0 = e; s0 < n && met < cnt; s0 += 64 * kInputBatch) {
-      unsigned long long hits[kInputBatch];
-      if (cnt == 1) {
-#pragma unroll
-        for (int u = 0; u < kInputBatch; ++u) hits[u] = u == 0 ? 1ull : 0ull;
+  for (int u = 0; u < NU; ++u) {
+    const unsigned long long hb = __ballot(x[u] == r && 64 * u + lane < n);
+    if (hb != 0ull) {
+      if (x[u] == r && 64 * u + lane < n)
+        list[w][cnt + __popcll(hb & ((1ull << lane) - 1ull))] = (unsigned short)(64 * u + lane);
+      if (cnt == 0) first = 64 * u + __ffsll((unsigned long long)hb) - 1;
+      if (e >= 64 * u + 64)
+        before += __popcll(hb);
+      else if (e >= 64 * u)
+        before += __popcll(hb & ((1ull << (e - 64 * u)) - 1ull));
+      cnt += __popcll(hb);
+    }
+  }
+  // the list is read back by other lanes of this wave (its LDS accesses
+  // complete in order)
+  asm volatile("" ::: "memory");
+  if (cnt < kInputHotSlots) {
+    if (first != e) return;
+    const int s = list[w][min(lane, cnt - 1)];
+    update_row<VEC>(W, gA, d, r, cnt, val[s], (unsigned)(s / K) * (unsigned)d, lr);
+    return;
+  }
+  if (64 * before >= d) return;
+  const int col = 64 * before + lane, colc = min(col, d - 1);
+  const float old = W[(size_t)r * d + colc];
+  float acc = 0.f;
+  for (int t0 = 0; t0 < cnt; t0 += 64) {
+    const int s = list[w][min(t0 + lane, cnt - 1)];
+    acc += sum_list_col(gA, colc, min(64, cnt - t0), val[s], (unsigned)(s / K) * (unsigned)d);
+  }
+  if (col < d) W[(size_t)r * d + col] = old - lr * acc;
+}
+
+// Ascending order of one key per thread over the block (bitonic; strides below
+// 64 by shuffles, the others through LDS).
+__device__ __forceinline__ unsigned long long block_sort_asc(unsigned long long x,
+                                                             unsigned long long* sh) {
+  const int t = threadIdx.x;
+  for (int k = 2; k <= kSortBlock; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      unsigned long long o;
+      if (j >= 64) {
+        sh[t] = x;
+        __syncthreads();
+        o = sh[t ^ j];
+        __syncthreads();
       } else {
-        int x[kInputBatch];
+        o = __shfl_xor(x, j);
+      }
+      const bool up = (t & k) == 0, low = (t & j) == 0;
+      x = (low == up) ? (o < x ? o : x) : (o > x ? o : x);
+    }
+  }
+  return x;
+}
+
+// Block b sorts slots [1024 b, +1024) by (row, slot) and counts each run in the
+// table; a row is listed as its second run arrives.
+__global__ __launch_bounds__(kSortBlock) void input_group_kernel(
+    const int32_t* __restrict__ idx, const float* __restrict__ val, int n, int K, int d, int64_t D,
+    int* srow, uint2* spair, int* rlen, int* rent, int* piv, unsigned long long* table,
+    int* multi, int4* part, int* flags) {
+  __shared__ unsigned long long sh[kSortBlock];
+  __shared__ unsigned long long heads[kSortBlock / 64];
+  const int t = threadIdx.x, e = blockIdx.x * kSortBlock + t;
+  if (e == 0) part[0] = make_int4(0, 0, 0, 0);
+  const int r = e < n ? idx[e] : -1;
+  if (r < -1 || (int64_t)r >= D) atomicCAS(flags, 0, LST_EINDEX);
+  const bool valid = r >= 0 && (int64_t)r < D;
+  const unsigned row = valid ? (unsigned)r : 0xffffffffu;  // the others last
+  const unsigned long long x =
+      block_sort_asc(((unsigned long long)row << 32) | (unsigned)e, sh);
+  sh[t] = x;
+  __syncthreads();
+  const unsigned my = (unsigned)(x >> 32);
+  const int slot = (int)(unsigned)x;
+  const float v = slot < n ? val[slot] : 0.f;
+  const bool head = my != 0xffffffffu && (t == 0 || (unsigned)(sh[t - 1] >> 32) != my);
+  const bool end = my == 0xffffffffu;  // no run: ends the one before
+  const unsigned long long stop = __ballot(head || end);
+  if ((t & 63) == 0) heads[t >> 6] = stop;
+  __syncthreads();
+  int len = 0, ent = -1;
+  if (head) {
+    // up to the next head (or the end of the valid slots)
+    int nx = kSortBlock;
+    unsigned long long m = heads[t >> 6] & (~0ull << (t & 63)) & ~(1ull << (t & 63));
+    for (int q = t >> 6; q < kSortBlock / 64; ++q) {
+      if (q > (t >> 6)) m = heads[q];
+      if (m != 0ull) {
+        nx = 64 * q + __ffsll((unsigned long long)m) - 1;
+        break;
+      }
+    }
+    len = nx - t;
+  }
+  // the position's arrays are whole blocks (kInputMaxSlots is a multiple of 1024)
+  const int row_out = end ? 0x7fffffff : (int)my;
+  srow[e] = row_out;
+  spair[e] = make_uint2((unsigned)(slot / K) * (unsigned)d, __float_as_uint(v));
+  rlen[e] = len;
+  if ((t & 63) == 63) piv[e >> 6] = row_out;
+  if ((t & 15) == 15) piv[kInputMaxSlots / 64 + (e >> 4)] = row_out;
+  if (head) {
+    // a new row: one atomic; a row that another block has entered: one more
+    unsigned h = input_hash((int)my);
+    const unsigned long long mine = ((unsigned long long)my << 32) | 1ull;
+    for (int probe = 0; probe < kInputHashSize; ++probe) {
+      const unsigned long long prev = atomicCAS(table + h, kNoEntry, mine);
+      if (prev == kNoEntry || (unsigned)(prev >> 32) == my) {
+        ent = (int)h;
+        if (prev != kNoEntry && (unsigned)atomicAdd(table + h, 1ull) == 1u)
+          multi[1 + atomicAdd(multi, 1)] = (int)h;
+        break;
+      }
+      h = (h + 1) & (kInputHashSize - 1);
+    }
+  }
+  rent[e] = ent;
+}
+
+// Block b's run of row r: its first position in q, its length returned (0:
+// none).  Four dependent loads: the block's sixteen groups of 64 by their last
+// rows, the group's four of 16, the sixteen rows, the length.
+__device__ __forceinline__ int below(const int4& x, int r) {
+  return (x.x < r) + (x.y < r) + (x.z < r) + (x.w < r);
+}
+__device__ __forceinline__ int find_run(const int* srow, const int* rlen, const int* piv, int b,
+                                        int nb, int r, int& q) {
+  q = 0;
+  if (b >= nb) return 0;
+  constexpr int kGroups = kSortBlock / 64;
+  const int4* p64 = reinterpret_cast<const int4*>(piv + b * kGroups);
+  int grp = 0;
 #pragma unroll
-        for (int u = 0; u < kInputBatch; ++u) {
-          const int s = s0 + 64 * u + lane;
-          x[u] = s < n ? idx[s] : -1;
+  for (int u = 0; u < kGroups / 4; ++u) grp += below(p64[u], r);
+  if (grp == kGroups) return 0;
+  grp += b * kGroups;
+  const int sub =
+      4 * grp + below(reinterpret_cast<const int4*>(piv + kInputMaxSlots / 64)[grp], r);
+  const int4* sr = reinterpret_cast<const int4*>(srow + 16 * sub);
+  int lt = 0;
+  bool eq = false;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int4 x = sr[u];
+    lt += below(x, r);
+    eq |= x.x == r || x.y == r || x.z == r || x.w == r;
+  }
+  if (!eq) return 0;
+  q = 16 * sub + lt;
+  return rlen[q];
+}
+
+// Exclusive prefix sum over the wave (every lane takes part); total in all lanes.
+__device__ __forceinline__ int wave_prefix(int v, int& total) {
+  const int lane = threadIdx.x & 63;
+  int s = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(s, off);
+    if (lane >= off) s += o;
+  }
+  total = __builtin_amdgcn_readlane(s, 63);
+  return s - v;
+}
+
+// Sorted positions of one wave: their runs are looked up together, one a lane.
+// 4: at the largest Zipf 1.1 call 81 us for update and forward pass, 92 at 16
+// (too few waves for the rows of one slot); with uniform rows 126, 155 at 1.
+constexpr int kRunsPerWave = 4;
+// Blocks (of four waves) for the rows that several blocks name.
+constexpr int kMultiBlocks = 1024;
+static_assert(kInputMaxSlots / 2 <= 4 * kMultiBlocks * 64, "a lane for each of a wave's rows");
+
+// Lists the parts of a row of total (>= kInputHotSlots) slots; every lane of
+// the wave takes part.
+__device__ __forceinline__ void list_parts(int row, int total, int4* part, int4* split) {
+  const int lane = threadIdx.x & 63;
+  const int np = (total + kPartSlots - 1) / kPartSlots;
+  int at = 0, sum = 0;
+  if (lane == 0) {
+    at = 1 + atomicAdd(&part->x, np);
+    if (np > 1) {
+      sum = atomicAdd(&part->z, np);
+      split[atomicAdd(&part->y, 1)] = make_int4(row, sum, np, 0);
+    }
+  }
+  at = __builtin_amdgcn_readlane(at, 0);
+  sum = __builtin_amdgcn_readlane(sum, 0);
+  for (int j = lane; j < np; j += 64) part[at + j] = make_int4(row, j, total, sum);
+}
+
+// Positions [p0, p0 + kRunsPerWave): the runs whose row no other block names.
+template <bool VEC>
+__device__ __forceinline__ void update_runs(float* W, const float* gA, int d, float lr, int p0,
+                                            const int* srow, const uint2* spair, const int* rlen,
+                                            const int* rent, unsigned long long* table, int4* part,
+                                            int4* split, int pending) {
+  const int lane = threadIdx.x & 63;
+  const int p = p0 + min(lane, kRunsPerWave - 1);
+  int len = rlen[p];
+  const int r = srow[p], h = rent[p];
+  const uint2 pr = spair[p];
+  bool mine = false;
+  if (lane < kRunsPerWave && len > 0 && h >= 0) {
+    if ((unsigned)table[h] == 1u) {
+      mine = true;
+      table[h] = kNoEntry;
+    }
+  }
+  if (pending != 0) return;
+  unsigned long long many = __ballot(mine && len >= kInputHotSlots);
+  while (many != 0ull) {
+    const int l = __ffsll((unsigned long long)many) - 1;
+    many &= many - 1;
+    list_parts(__builtin_amdgcn_readlane(r, l), __builtin_amdgcn_readlane(len, l), part, split);
+  }
+  // rows of one slot, kListRows / 2 at a time
+  unsigned long long todo = __ballot(mine && len == 1);
+  constexpr int kS = kListRows / 2;
+  while (todo != 0ull) {
+    int rr[kS];
+    float vv[kS];
+    unsigned oo[kS];
+    int cnt = 0;
+#pragma unroll
+    for (int u = 0; u < kS; ++u) {
+      const bool on = todo != 0ull;
+      const int l = on ? __ffsll((unsigned long long)todo) - 1 : 0;
+      if (on) {
+        rr[u] = __builtin_amdgcn_readlane(r, l);
+        vv[u] = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)pr.y, l));
+        oo[u] = (unsigned)__builtin_amdgcn_readlane((int)pr.x, l);
+        ++cnt;
+      } else {  // the first one again (never stored)
+        rr[u] = rr[0];
+        vv[u] = 0.f;
+        oo[u] = oo[0];
+      }
+      todo &= todo - 1;
+    }
+    for (int cg = 0; cg < d; cg += 512) {
+      float4 old[kS][2], g[kS][2];
+#pragma unroll
+      for (int u = 0; u < kS; ++u)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int col = cg + 256 * c + 4 * lane;
+          old[u][c] = row_load4<VEC>(W + (size_t)rr[u] * d, col, d);
+          g[u][c] = row_load4<VEC>(gA + oo[u], col, d);
         }
 #pragma unroll
-        for (int u = 0; u < kInputBatch; ++u) hits[u] = __ballot(x[u] == r);
-      }
+      for (int u = 0; u < kS; ++u) {
+        if (u >= cnt) break;
 #pragma unroll
-      for (int u = 0; u < kInputBatch; ++u) {
-        unsigned long long hb = hits[u];
-        met += __popcll(hb);
-        // kInputRows slots at a time: their rows of dA are in flight together
-        while (hb) {
-          int t[kInputRows];
-          bool on[kInputRows];
-#pragma unroll
-          for (int q = 0; q < kInputRows; ++q) {
-            on[q] = hb != 0;
-            t[q] = s0 + 64 * u + (on[q] ? __ffsll((long long)hb) - 1 : 0);
-            hb &= hb - 1;
-          }
-          float v[kInputRows];
-          float4 g[kInputRows][4];
-#pragma unroll
-          for (int q = 0; q < kInputRows; ++q) {
-            v[q] = val[on[q] ? t[q] : e];
-            const float* gr = gA + (size_t)((on[q] ? t[q] : e) / K) * d;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const int col = cg + 256 * c + 4 * lane;
-              g[q][c] = make_float4(0.f, 0.f, 0.f, 0.f);
-              if (c < nc && col < d) {
-                if (vec) {
-                  g[q][c] = *reinterpret_cast<const float4*>(gr + col);
-                } else {
-                  g[q][c].x = gr[col];
-                  if (col + 1 < d) g[q][c].y = gr[col + 1];
-                  if (col + 2 < d) g[q][c].z = gr[col + 2];
-                  if (col + 3 < d) g[q][c].w = gr[col + 3];
-                }
-              }
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < kInputRows; ++q) {
-            if (!on[q]) break;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              acc[c].x += v[q] * g[q][c].x; acc[c].y += v[q] * g[q][c].y;
-              acc[c].z += v[q] * g[q][c].z; acc[c].w += v[q] * g[q][c].w;
-            }
-          }
+        for (int c = 0; c < 2; ++c) {
+          old[u][c].x -= lr * (vv[u] * g[u][c].x); old[u][c].y -= lr * (vv[u] * g[u][c].y);
+          old[u][c].z -= lr * (vv[u] * g[u][c].z); old[u][c].w -= lr * (vv[u] * g[u][c].w);
+          row_store4<VEC>(W + (size_t)rr[u] * d, cg + 256 * c + 4 * lane, d, old[u][c]);
         }
       }
     }
-    float* row = W + (size_t)r * d;
+  }
+  // rows of several slots, one after another (the run's slots are in order)
+  unsigned long long more = __ballot(mine && len > 1 && len < kInputHotSlots);
+  while (more != 0ull) {
+    const int l = __ffsll((unsigned long long)more) - 1;
+    more &= more - 1;
+    const int cnt = __builtin_amdgcn_readlane(len, l);
+    const uint2 x = spair[p0 + l + min(lane, cnt - 1)];
+    update_row<VEC>(W, gA, d, __builtin_amdgcn_readlane(r, l), cnt, __uint_as_float(x.y), x.x, lr);
+  }
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void input_update_kernel(
+    float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
+    const uint2* spair, const int* rlen, const int* rent, const int* piv,
+    unsigned long long* table, const int* multi, int4* part, int4* split, const int* flags) {
+  __shared__ uint2 list[4][kInputHotSlots];
+  const int w = wave_index(), lane = threadIdx.x & 63;
+  const int nb = (n + kSortBlock - 1) / kSortBlock;
+  const int pending = *flags;
+  if (blockIdx.x >= kMultiBlocks) {
+    const int p0 = (((int)blockIdx.x - kMultiBlocks) * 4 + w) * kRunsPerWave;
+    if (p0 >= nb * kSortBlock) return;
+    update_runs<VEC>(W, gA, d, lr, p0, srow, spair, rlen, rent, table, part, split, pending);
+    return;
+  }
+  // The listed rows wv, wv + nw, ...: one a lane, then one after another.
+  const int wv = (int)blockIdx.x * 4 + w, nw = 4 * kMultiBlocks;
+  const int count = multi[0];
+  const int at = wv + nw * lane;
+  int row = -1;
+  if (at < count) {
+    const int h = multi[1 + at];
+    row = (int)(table[h] >> 32);
+    table[h] = kNoEntry;
+  }
+  if (pending != 0) return;
+  for (int l = 0; wv + nw * l < count; ++l) {
+    const int r = __builtin_amdgcn_readlane(row, l);
+    int q, total;
+    const int mine = find_run(srow, rlen, piv, lane, nb, r, q);
+    const int off = wave_prefix(mine, total);
+    if (total >= kInputHotSlots) {
+      list_parts(r, total, part, split);
+      continue;
+    }
+    for (int u = 0; u < mine; ++u) list[w][off + u] = spair[q + u];
+    // the list is read back by other lanes of this wave (its LDS accesses
+    // complete in order)
+    asm volatile("" ::: "memory");
+    const uint2 x = list[w][min(lane, total - 1)];
+    update_row<VEC>(W, gA, d, r, total, __uint_as_float(x.y), x.x, lr);
+    asm volatile("" ::: "memory");
+  }
+}
+
+// Blocks of the hot rows' launches; they take the parts (the rows) in turn.
+constexpr int kHotBlocks = 1024;
+
+// One part: kPartSlots slots of a hot row, in order, 64 to each wave; the four
+// sums are added in wave order.  The row itself is updated if this is all of it.
+template <bool VEC>
+__global__ __launch_bounds__(256) void input_hot_kernel(
+    float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
+    const uint2* spair, const int* rlen, const int* piv, int* multi, const int4* part, float* psum,
+    const int* flags) {
+  __shared__ float4 sums[3][2][64];
+  __shared__ int s_off[64], s_q[64];
+  const int nb = (n + kSortBlock - 1) / kSortBlock;
+  const int w = wave_index(), lane = threadIdx.x & 63;
+  if (blockIdx.x == 0 && threadIdx.x == 0) multi[0] = 0;  // its rows are done
+  const int count = *flags != 0 ? 0 : part[0].x;
+  for (int b = blockIdx.x; b < count; b += gridDim.x) {
+    const int4 pt = part[1 + b];
+    const int r = __builtin_amdgcn_readfirstlane(pt.x), j = __builtin_amdgcn_readfirstlane(pt.y),
+              total = __builtin_amdgcn_readfirstlane(pt.z),
+              sum0 = __builtin_amdgcn_readfirstlane(pt.w);
+    if (w == 0) {
+      int q, all;
+      const int mine = find_run(srow, rlen, piv, lane, nb, r, q);
+      s_off[lane] = wave_prefix(mine, all);
+      s_q[lane] = q;
+    }
+    __syncthreads();
+    const int tb = j * kPartSlots + 64 * w, te = min(total, tb + 64);
+    uint2 x = make_uint2(0u, 0u);
+    if (tb < te) {
+      const int t = min(tb + lane, te - 1);
+      int lo = 0;  // the last block whose first slot is not after t
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int col = cg + 256 * c + 4 * lane;
-      if (c >= nc || col >= d) continue;
-      row[col] -= lr * acc[c].x;
-      if (col + 1 < d) row[col + 1] -= lr * acc[c].y;
-      if (col + 2 < d) row[col + 2] -= lr * acc[c].z;
-      if (col + 3 < d) row[col + 3] -= lr * acc[c].w;
+      for (int s = 32; s > 0; s >>= 1)
+        if (s_off[lo + s] <= t) lo += s;
+      x = spair[s_q[lo] + t - s_off[lo]];
+    }
+    const bool whole = total <= kPartSlots;
+    float* out = whole ? W + (size_t)r * d : psum + (size_t)(sum0 + j) * d;
+    for (int cg = 0; cg < d; cg += 512) {
+      float4 acc[2], old[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        acc[c] = old[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (w == 0 && whole) old[c] = row_load4<VEC>(out, cg + 256 * c + 4 * lane, d);
+      }
+      if (tb < te) sum_list<VEC>(gA, d, cg, te - tb, __uint_as_float(x.y), x.x, acc);
+      if (w > 0) {
+        sums[w - 1][0][lane] = acc[0];
+        sums[w - 1][1][lane] = acc[1];
+      }
+      __syncthreads();
+      if (w == 0) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+          for (int v = 0; v < 3; ++v) {
+            const float4 o = sums[v][c][lane];
+            acc[c].x += o.x; acc[c].y += o.y; acc[c].z += o.z; acc[c].w += o.w;
+          }
+          if (whole) {
+            acc[c].x = old[c].x - lr * acc[c].x; acc[c].y = old[c].y - lr * acc[c].y;
+            acc[c].z = old[c].z - lr * acc[c].z; acc[c].w = old[c].w - lr * acc[c].w;
+          }
+          row_store4<VEC>(out, cg + 256 * c + 4 * lane, d, acc[c]);
+        }
+      }
+      __syncthreads();
     }
   }
 }
 
-// Block b (1024 threads) sums the hot row hot[1 + b / nch] over columns
-// [256 (b % nch), +256): wave w adds v dA over the slots of the w-th sixteenth
-// of [0, n) that hold the row, in slot order; the sixteen partial sums are then
-// added in wave order and the row is updated once.  Blocks past the number of
-// hot rows exit.
-__global__ __launch_bounds__(1024) void input_hot_kernel(float* __restrict__ W, int d,
-                                                         const int32_t* __restrict__ idx,
-                                                         const float* __restrict__ val,
-                                                         const float* __restrict__ gA, int n,
-                                                         int K, float lr, const int* hot,
-                                                         const int* flags) {
-  __shared__ float4 part[16][64];
-  const int nch = (d + 255) / 256;
-  const int hid = blockIdx.x / nch;
-  if (hid >= hot[0] || *flags) return;
-  const int r = hot[1 + hid];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int col = (blockIdx.x % nch) * 256 + 4 * lane;
-  const bool vec = (d % 4 == 0);
-  const int span = (n + 15) / 16, sb = wave * span, se = min(n, sb + span);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = sb; s0 < se; s0 += 64 * kInputBatch) {
-    unsigned long long hits[kInputBatch];
-    {
-      int x[kInputBatch];
+// Rows of several parts: a wave per (row, 64 columns) adds the parts' sums in
+// order, sixteen in flight, and updates the row.
+__global__ __launch_bounds__(256) void input_split_kernel(float* __restrict__ W, int d, float lr,
+                                                          const int4* part, const int4* split,
+                                                          const float* psum, const int* flags) {
+  const int nch = (d + 63) / 64;
+  const int w = wave_index(), lane = threadIdx.x & 63;
+  const int count = *flags != 0 ? 0 : part[0].y;
+  for (int b = (int)blockIdx.x * 4 + w; b < count * nch; b += 4 * gridDim.x) {
+    const int4 sp = split[b / nch];
+    const int col = (b % nch) * 64 + lane, colc = min(col, d - 1), np = sp.z;
+    float* out = W + (size_t)sp.x * d + colc;
+    const float old = *out;
+    const float* ps = psum + (size_t)sp.y * d + colc;
+    float acc = 0.f;
+    for (int j0 = 0; j0 < np; j0 += 16) {
+      float g[16];
 #pragma unroll
-      for (int u = 0; u < kInputBatch; ++u) {
-        const int s = s0 + 64 * u + lane;
-        x[u] = s < se ? idx[s] : -1;
-      }
+      for (int u = 0; u < 16; ++u) g[u] = ps[(size_t)min(j0 + u, np - 1) * d];
 #pragma unroll
-      for (int u = 0; u < kInputBatch; ++u) hits[u] = __ballot(x[u] == r);
+      for (int u = 0; u < 16; ++u) acc += j0 + u < np ? g[u] : 0.f;
     }
-#pragma unroll
-    for (int u = 0; u < kInputBatch; ++u) {
-      unsigned long long hb = hits[u];
-      while (hb) {
-        int t[kInputRows];
-        bool on[kInputRows];
-#pragma unroll
-        for (int q = 0; q < kInputRows; ++q) {
-          on[q] = hb != 0;
-          t[q] = s0 + 64 * u + (on[q] ? __ffsll((long long)hb) - 1 : 0);
-          hb &= hb - 1;
-        }
-        float v[kInputRows];
-        float4 g[kInputRows];
-#pragma unroll
-        for (int q = 0; q < kInputRows; ++q) {
-          const int tq = on[q] ? t[q] : sb;
-          v[q] = val[tq];
-          const float* gr = gA + (size_t)(tq / K) * d;
-          g[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (on[q] && col < d) {
-            if (vec) {
-              g[q] = *reinterpret_cast<const float4*>(gr + col);
-            } else {
-              g[q].x = gr[col];
-              if (col + 1 < d) g[q].y = gr[col + 1];
-              if (col + 2 < d) g[q].z = gr[col + 2];
-              if (col + 3 < d) g[q].w = gr[col + 3];
-            }
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < kInputRows; ++q) {
-          if (!on[q]) break;
-          acc.x += v[q] * g[q].x; acc.y += v[q] * g[q].y;
-          acc.z += v[q] * g[q].z; acc.w += v[q] * g[q].w;
-        }
-      }
-    }
+    if (col < d) *out = old - lr * acc;
   }
-  part[wave][lane] = acc;
-  __syncthreads();
-  if (wave != 0) return;
-  float4 sum = part[0][lane];
-  for (int w = 1; w < 16; ++w) {
-    const float4 o = part[w][lane];
-    sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
-  }
-  float* row = W + (size_t)r * d;
-  if (col < d) row[col] -= lr * sum.x;
-  if (col + 1 < d) row[col + 1] -= lr * sum.y;
-  if (col + 2 < d) row[col + 2] -= lr * sum.z;
-  if (col + 3 < d) row[col + 3] -= lr * sum.w;
 }
 
 int check_batch(lst_input* s, int32_t m, int32_t K, const int32_t* idx, const float* val) {
@@ -483,8 +794,9 @@ int lst_input_init(lst_input** out, int64_t D_in, int32_t d, const float* W_in,
   s->stream = static_cast<hipStream_t>(hip_stream);
   auto fail = [&](int code) {
     (void)hipStreamSynchronize(s->stream);
-    for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->hkey, (void*)s->hmin, (void*)s->hcnt,
-                    (void*)s->own, (void*)s->hot})
+    for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->table,
+                    (void*)s->srow, (void*)s->spair, (void*)s->rlen, (void*)s->rent,
+                    (void*)s->piv, (void*)s->multi, (void*)s->part, (void*)s->split, (void*)s->psum})
       if (p) (void)hipFree(p);
     delete s;
     return code;
@@ -492,14 +804,19 @@ int lst_input_init(lst_input** out, int64_t D_in, int32_t d, const float* W_in,
   if (hipGetDevice(&s->device) != hipSuccess) return fail(LST_EHIP);
   if (hipMalloc((void**)&s->W, (size_t)D_in * d * sizeof(float)) != hipSuccess ||
       hipMalloc((void**)&s->flags, sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->hkey, kInputHashSize * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->hmin, kInputHashSize * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->hcnt, kInputHashSize * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->own, kInputMaxSlots * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->hot, (1 + kInputMaxHot) * sizeof(int)) != hipSuccess)
+      hipMalloc((void**)&s->table, kInputHashSize * sizeof(unsigned long long)) != hipSuccess ||
+      hipMalloc((void**)&s->srow, kInputMaxSlots * sizeof(int)) != hipSuccess ||
+      hipMalloc((void**)&s->spair, kInputMaxSlots * sizeof(uint2)) != hipSuccess ||
+      hipMalloc((void**)&s->piv, (kInputMaxSlots / 64 + kInputMaxSlots / 16) * sizeof(int)) != hipSuccess ||
+      hipMalloc((void**)&s->multi, (1 + kInputMaxSlots / 2) * sizeof(int)) != hipSuccess ||
+      hipMalloc((void**)&s->rlen, kInputMaxSlots * sizeof(int)) != hipSuccess ||
+      hipMalloc((void**)&s->rent, kInputMaxSlots * sizeof(int)) != hipSuccess ||
+      hipMalloc((void**)&s->part, (1 + kMaxParts) * sizeof(int4)) != hipSuccess ||
+      hipMalloc((void**)&s->split, kMaxSplit * sizeof(int4)) != hipSuccess ||
+      hipMalloc((void**)&s->psum, (size_t)kMaxSums * d * sizeof(float)) != hipSuccess)
     return fail(LST_ENOMEM);
   hipLaunchKernelGGL(input_table_init_kernel, dim3(kInputHashSize / 256), dim3(256), 0, s->stream,
-                     s->hkey, s->hmin, s->hcnt, s->own, s->hot);
+                     s->table, s->multi);
   if (hipMemsetAsync(s->flags, 0, sizeof(int), s->stream) != hipSuccess ||
       hipMemcpyAsync(s->W, W_in, (size_t)D_in * d * sizeof(float), hipMemcpyDeviceToDevice,
                      s->stream) != hipSuccess ||
@@ -515,24 +832,24 @@ int lst_input_forward(lst_input* s, int32_t m, int32_t K, const int32_t* idx, co
   if (rc != LST_OK) return rc;
   if (!A) return LST_EINVAL;
   DeviceScope g(s->device);
-  const int n = m * K;
-  hipLaunchKernelGGL(input_validate_kernel, dim3((n + 255) / 256), dim3(256), 0, s->stream, idx,
-                     n, s->D, s->flags);
+  const int nch = (s->d + 255) / 256;
   const bool vec = (s->d % 4 == 0) && (((uintptr_t)A & 15) == 0);
   if (K > kInputSplitK) {
-    const dim3 grid((unsigned)(m * ((s->d + 255) / 256)));
+    const dim3 grid((unsigned)(m * nch));
     if (vec)
       hipLaunchKernelGGL(input_forward_split_kernel<true>, grid, dim3(256), 0, s->stream, s->W,
-                         s->D, s->d, idx, val, m, K, A);
+                         s->D, s->d, idx, val, m, K, A, s->flags);
     else
       hipLaunchKernelGGL(input_forward_split_kernel<false>, grid, dim3(256), 0, s->stream, s->W,
-                         s->D, s->d, idx, val, m, K, A);
-  } else if (vec) {
-    hipLaunchKernelGGL(input_forward_kernel<true>, dim3((m + 3) / 4), dim3(256), 0, s->stream,
-                       s->W, s->D, s->d, idx, val, m, K, A);
+                         s->D, s->d, idx, val, m, K, A, s->flags);
   } else {
-    hipLaunchKernelGGL(input_forward_kernel<false>, dim3((m + 3) / 4), dim3(256), 0, s->stream,
-                       s->W, s->D, s->d, idx, val, m, K, A);
+    const dim3 grid((unsigned)((m * nch + 3) / 4));
+    if (vec)
+      hipLaunchKernelGGL(input_forward_kernel<true>, grid, dim3(256), 0, s->stream, s->W, s->D,
+                         s->d, idx, val, m, K, A, s->flags);
+    else
+      hipLaunchKernelGGL(input_forward_kernel<false>, grid, dim3(256), 0, s->stream, s->W, s->D,
+                         s->d, idx, val, m, K, A, s->flags);
   }
   return hipGetLastError() == hipSuccess ? LST_OK : LST_EHIP;
 }
@@ -544,19 +861,42 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
   if (!grad_A || !(lr > 0.f) || !isfinite(lr)) return LST_EINVAL;
   DeviceScope g(s->device);
   const int n = m * K;
-  hipLaunchKernelGGL(input_insert_kernel, dim3((n + 255) / 256), dim3(256), 0, s->stream, idx, n,
-                     s->D, s->hkey, s->hmin, s->hcnt, s->flags);
-  hipLaunchKernelGGL(input_update_kernel, dim3((n + 3) / 4), dim3(256), 0, s->stream, s->W, s->D,
-                     s->d,
-                     idx, val, grad_A, n, K, lr, s->hkey, s->hmin, s->hcnt, s->own, s->hot,
-                     s->flags);
-  if (n >= kInputHotSlots) {
-    const int nch = (s->d + 255) / 256;
-    hipLaunchKernelGGL(input_hot_kernel, dim3((unsigned)((n / kInputHotSlots) * nch)), dim3(1024),
-                       0, s->stream, s->W, s->d, idx, val, grad_A, n, K, lr, s->hot, s->flags);
+  const bool vec = (s->d % 4 == 0) && (((uintptr_t)grad_A & 15) == 0);
+  if (n <= kInputSmall) {
+    const dim3 grid((unsigned)((n + 3) / 4));
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s->stream, s->W, s->D, s->d, idx, val, grad_A,
+                         n, K, lr, s->flags);
+    };
+    if (n <= 64 * 4)
+      vec ? run(input_update_small_kernel<4, true>) : run(input_update_small_kernel<4, false>);
+    else
+      vec ? run(input_update_small_kernel<kInputSmall / 64, true>)
+          : run(input_update_small_kernel<kInputSmall / 64, false>);
+    return hipGetLastError() == hipSuccess ? LST_OK : LST_EHIP;
   }
-  hipLaunchKernelGGL(input_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s->stream, s->own, n,
-                     s->hkey, s->hmin, s->hcnt, s->hot);
+  const int nb = (n + kSortBlock - 1) / kSortBlock;
+  hipLaunchKernelGGL(input_group_kernel, dim3(nb), dim3(kSortBlock), 0, s->stream, idx, val, n, K,
+                     s->d, s->D, s->srow, s->spair, s->rlen, s->rent, s->piv, s->table, s->multi,
+                     s->part, s->flags);
+  const dim3 grid((unsigned)(kMultiBlocks + nb * kSortBlock / (4 * kRunsPerWave)));
+  auto update = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s->stream, s->W, s->d, grad_A, n, lr, s->srow,
+                       s->spair, s->rlen, s->rent, s->piv, s->table, s->multi, s->part, s->split,
+                       s->flags);
+  };
+  vec ? update(input_update_kernel<true>) : update(input_update_kernel<false>);
+  const int parts = n / kInputHotSlots + n / kPartSlots;  // at most
+  auto hot = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(parts, kHotBlocks)), dim3(256), 0,
+                       s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair, s->rlen, s->piv,
+                       s->multi, s->part, s->psum, s->flags);
+  };
+  vec ? hot(input_hot_kernel<true>) : hot(input_hot_kernel<false>);
+  const int most = (n / kPartSlots) * ((s->d + 63) / 64);
+  hipLaunchKernelGGL(input_split_kernel, dim3((unsigned)std::min((most + 3) / 4, kHotBlocks)),
+                     dim3(256), 0, s->stream, s->W, s->d, lr, s->part, s->split, s->psum,
+                     s->flags);
   return hipGetLastError() == hipSuccess ? LST_OK : LST_EHIP;
 }
 
@@ -588,8 +928,9 @@ void lst_input_free(lst_input* s) {
   if (!s) return;
   DeviceScope g(s->device);
   (void)hipStreamSynchronize(s->stream);
-  for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->hkey, (void*)s->hmin, (void*)s->hcnt,
-                  (void*)s->own, (void*)s->hot})
+  for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->table,
+                  (void*)s->srow, (void*)s->spair, (void*)s->rlen, (void*)s->rent,
+                  (void*)s->piv, (void*)s->multi, (void*)s->part, (void*)s->split, (void*)s->psum})
     (void)hipFree(p);
   delete s;
 }

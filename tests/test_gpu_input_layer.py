@@ -106,3 +106,90 @@ def test_input_layer_bad_index_leaves_W(gpu_lib):
     W_ref = input_layer.update(W.astype(np.float64), idx1, val1, G1, 0.1)
     assert rel(layer.get_W().cpu().numpy(), W_ref) < 1e-6
     layer.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(m=1, K=1, d=5, D=3),                                  # the smallest call
+    dict(m=64, K=4, d=64, D=40),                               # 256 slots: the short small form
+    dict(m=257, K=1, d=30, D=100),
+    dict(m=128, K=16, d=258, D=60),                            # 2048: one launch, hot rows
+    dict(m=683, K=3, d=500, D=1000),                           # 2049: the grouped form
+    dict(m=1, K=2048, d=513, D=7),                             # every row hot
+    dict(m=1, K=2100, d=1030, D=9),
+    dict(m=61, K=63, d=64, D=5000, idx_dist="zipf", zipf_s=1.1),
+    dict(m=1024, K=64, d=36, D=50),                            # every row hot, all 64 blocks
+    dict(m=4096, K=16, d=20, D=30000, idx_dist="zipf", zipf_s=1.0),
+    dict(m=65535, K=1, d=12, D=1),                             # one row, every slot
+])
+def test_input_layer_forms_and_edges(gpu_lib, kw):
+    """The update's forms at their edges (256, 2048 slots; 64 slots a row; 1024 slots a
+    sorted block), with pads and repeats; the forward pass at K = 16 and beyond.  A row's sum
+    of n products is off by at most n eps times the sum of their magnitudes, which for terms
+    of random sign is sqrt(n) times the result: 2^-24 sqrt(n) n^(1/2) over partial sums of
+    32 and 16 parts stays below 1e-5 up to n = 65 536."""
+    cfg = WorkloadConfig(name="inpf", distinct=False, val_dist="normal", pad_frac=0.15,
+                         dup_frac=0.2, entropy=4500 + kw["m"] + 7 * kw["K"] + kw["d"],
+                         **{"idx_dist": "uniform", **kw})
+    import torch
+
+    wl = Workload(cfg)
+    W = wl.init_V()
+    layer = _layer(W)
+    W_ref = W.astype(np.float64)
+    for s in range(2):
+        G, idx, val = wl.batch(s)
+        i_t, v_t = torch.from_numpy(idx).cuda(), torch.from_numpy(val).cuda()
+        A = layer.forward(i_t, v_t).cpu().numpy().astype(np.float64)
+        W_prev = layer.get_W().cpu().numpy()
+        layer.update(i_t, v_t, torch.from_numpy(G).cuda(), 0.01)
+        assert layer.sync() == 0
+        W_new = layer.get_W().cpu().numpy()
+        A_ref, dW = np.zeros((cfg.m, cfg.d)), np.zeros((cfg.D, cfg.d))
+        rows, cols = np.nonzero(idx >= 0)
+        at = idx[rows, cols]
+        v64 = val[rows, cols].astype(np.float64)
+        np.add.at(A_ref, rows, v64[:, None] * W_prev[at].astype(np.float64))
+        np.add.at(dW, at, v64[:, None] * G[rows].astype(np.float64))
+        assert rel(A, A_ref) < 1e-6 + 2.0 ** -24 * np.sqrt(cfg.K), rel(A, A_ref)
+        W_ref = W_prev.astype(np.float64) - 0.01 * dW
+        touched = np.unique(at)
+        rest = np.setdiff1d(np.arange(cfg.D), touched)
+        assert np.array_equal(W_new[rest], W_prev[rest])
+        e = rel(W_new[touched] - W_prev[touched].astype(np.float64),
+                W_ref[touched] - W_prev[touched].astype(np.float64))
+        scale = np.abs(W_prev[touched]).max() / max(np.abs(0.01 * dW[touched]).max(), 1e-30)
+        print(f"{kw}: dW {e:.1e}", flush=True)
+        # the change itself, to the rounding of its sum and of W
+        assert e < 1e-5 + 2.0 ** -23 * scale, e
+        assert rel(W_new[touched], W_ref[touched]) < 1e-6
+    layer.close()
+
+
+@pytest.mark.parametrize("m,K", [(16, 8), (100, 30)])
+def test_input_layer_bad_index_both_forms(gpu_lib, m, K):
+    """A bad index in an update of one launch (128 slots) and of the grouped form (3000):
+    reported, W unchanged, the next call exact; the forward pass leaves its pair out."""
+    import torch
+
+    import paper_1412_7091_amd as lst
+
+    cfg = WorkloadConfig(name="inpbb", D=400, d=24, m=m, K=K, distinct=False, entropy=4600 + m)
+    wl = Workload(cfg)
+    W = wl.init_V()
+    layer = _layer(W)
+    G, idx, val = wl.batch(0)
+    bad = idx.copy()
+    bad[m // 2, 1], bad[m - 1, K - 1] = cfg.D, -2
+    t = [torch.from_numpy(x).cuda() for x in (bad, val, G)]
+    layer.update(*t, 0.1)
+    assert layer.sync() == lst.LST_EINDEX
+    assert np.array_equal(layer.get_W().cpu().numpy(), W)
+    A = layer.forward(t[0], t[1]).cpu().numpy()
+    assert layer.sync() == lst.LST_EINDEX
+    good = np.where((bad >= 0) & (bad < cfg.D), bad, -1)
+    assert rel(A, input_layer.forward(W.astype(np.float64), good, val)) < 1e-6
+    layer.update(torch.from_numpy(idx).cuda(), t[1], t[2], 0.1)
+    assert layer.sync() == 0
+    W_ref = input_layer.update(W.astype(np.float64), idx, val, G, 0.1)
+    assert rel(layer.get_W().cpu().numpy(), W_ref) < 1e-6
+    layer.close()
