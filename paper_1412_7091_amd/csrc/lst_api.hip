@@ -74,6 +74,7 @@ struct lst_state {
   // naive workspace
   float* O = nullptr;
   float* wsplit = nullptr;
+  double* nws = nullptr;  // row sums in chunks
   int naive_ksplit = 1;
   int64_t steps = 0;
   std::vector<void*> allocs;
@@ -1100,7 +1101,8 @@ int lst_naive_init(lst_state** out, int64_t D, int32_t d, const float* W, const 
   if (ks < 1) ks = 1;
   s->naive_ksplit = (int)ks;
   if ((rc = dalloc(s, &s->O, (size_t)m * D)) ||
-      (rc = dalloc(s, &s->wsplit, (size_t)ks * m * d)))
+      (rc = dalloc(s, &s->wsplit, (size_t)ks * m * d)) ||
+      (rc = dalloc(s, &s->nws, naive_ws_doubles(m))))
     return fail(rc);
   if (hipMemcpyAsync(s->V, W, (size_t)D * d * sizeof(float), hipMemcpyDeviceToDevice, s->stream) !=
       hipSuccess)
@@ -1125,7 +1127,7 @@ int lst_naive_step(lst_state* s, int32_t m, int32_t K, const float* H, const int
                                       s->O, (int)D, 1.f, 0.f, EPI_STORE),
                          st));
   HIPCHK(naive_rowstats(s->O, D, D, m, Y_idx, Y_val, K, s->cfg.loss, s->cfg.sph_eps, loss,
-                        s->flags, st));
+                        s->nws, s->flags, st));
   {  // grad_H = (dL/dO) W  (K = D, split over K)
     GemmProblem p = gemm_problem(L_NN, m, d, (int)D, vmat(s->O, (int)D, m), vmat(s->V, d, (int)D),
                                  s->wsplit, d, 1.f, 0.f, EPI_PARTIAL);

@@ -336,8 +336,11 @@ int stab_ksplit(int d);
 hipError_t stabilize_enqueue(const StabArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------- naive
+// ws: naive_ws_doubles(m) doubles.
+constexpr int kNaiveChunks = 64;  // chunks of a row of O, at most
+inline size_t naive_ws_doubles(int m_max) { return (size_t)m_max * (kNaiveChunks + 1); }
 hipError_t naive_rowstats(float* O, int64_t ldo, int64_t D, int m, const int32_t* idx,
                           const float* val, int K, int loss_kind, float eps, float* loss,
-                          int* flags, hipStream_t s);
+                          double* ws, int* flags, hipStream_t s);
 
 }  // namespace lst

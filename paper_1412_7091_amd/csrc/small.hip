@@ -226,77 +226,145 @@ hipError_t transpose_square(const float* A, float* At, int d, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Naive baseline (sections 2.3 and 3.1): one workgroup per example turns the
-// output row o_i = W h_i (stored in O) into dL/do_i / (2 for squared error):
+// Naive baseline (sections 2.3 and 3.1): the output row o_i = W h_i (stored in
+// O) becomes dL/do_i / (2 for squared error):
 //   squared:   O_i <- o_i - y_i,  loss_i = ||o_i - y_i||^2
 //   spherical: O_i <- (2/S) o_i + b e_c,  loss_i = -log(o_c^2+eps) + log S
 //   shifted:   O_i <- (2/S) (o_i + eps) - (2/u_c) e_c, u_c = o_c + eps,
 //              S = sum_j (o_j + eps)^2,  loss_i = -log(u_c^2) + log S
-// Sums run in fp64 in a fixed tree order.
+// Sums run in fp64 in a fixed order.  Bound by reading the m x D outputs, so a
+// row is cut into chunks, a workgroup each (m workgroups alone read 102 MB at
+// 1.3 TB/s: 78 us at m = 128, D = 200 000; in chunks 20 us and 5): the first
+// launch subtracts the targets and leaves a sum per chunk, the second adds the
+// row's sums (in every workgroup that needs them) and finishes.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void naive_rowstats_kernel(float* __restrict__ O, int64_t ldo,
-                                                              int64_t D,
-                                                              const int32_t* __restrict__ idx,
-                                                              const float* __restrict__ val, int K,
-                                                              int loss_kind, float eps,
-                                                              float* __restrict__ loss,
-                                                              int* flags) {
-  __shared__ double red[1024];
-  __shared__ int s_c;
-  const int i = blockIdx.x;
+int naive_chunks(int64_t D, int m) {
+  int64_t n = (2048 + m - 1) / m;
+  const int64_t most = (D + 1023) / 1024;
+  if (n > most) n = most;
+  return (int)(n < 1 ? 1 : n > kNaiveChunks ? kNaiveChunks : n);
+}
+
+__device__ __forceinline__ void chunk_range(int64_t D, int nch, int c, int64_t& b, int64_t& e) {
+  const int64_t per = (D + nch - 1) / nch;
+  b = c * per < D ? c * per : D;
+  e = b + per < D ? b + per : D;
+}
+
+__global__ __launch_bounds__(256) void naive_chunk_kernel(float* __restrict__ O, int64_t ldo,
+                                                          int64_t D, int nch,
+                                                          const int32_t* __restrict__ idx,
+                                                          const float* __restrict__ val, int K,
+                                                          int loss_kind, float eps,
+                                                          double* __restrict__ sums,
+                                                          double* __restrict__ oc, int* flags) {
+  __shared__ double red[256];
+  __shared__ int32_t skey[1024];
+  const int c = blockIdx.x, i = blockIdx.y, t = threadIdx.x;
+  int64_t b, e;
+  chunk_range(D, nch, c, b, e);
   float* o = O + (size_t)i * ldo;
-  if (threadIdx.x == 0) {
-    s_c = -1;
-    for (int k = 0; k < K; ++k) {
+  const double sh = loss_kind == LST_LOSS_SPHERICAL_SHIFTED ? (double)eps : 0.0;
+  if (loss_kind == LST_LOSS_SQUARED) {
+    for (int k = t; k < K; k += 256) {
       const int r = idx[(size_t)i * K + k];
-      const bool bad = (r < -1) || ((int64_t)r >= D) ||
-                       (loss_kind != LST_LOSS_SQUARED && r == -1);
-      if (bad) {
-        atomicCAS(flags + F_ERR, 0, LST_EINDEX);
-        continue;
-      }
+      if (c == 0 && (r < -1 || (int64_t)r >= D)) atomicCAS(flags + F_ERR, 0, LST_EINDEX);
+      skey[k] = r >= b && r < e ? r : -1;
+    }
+    __syncthreads();
+    // the first slot of a row subtracts the values of all of its slots, in order
+    for (int k = t; k < K; k += 256) {
+      const int r = skey[k];
       if (r < 0) continue;
-      if (loss_kind == LST_LOSS_SQUARED) {
-        o[r] -= val[(size_t)i * K + k];
-      } else if (k == 0) {
-        s_c = r;
+      bool first = true;
+      for (int q = 0; q < k && first; ++q) first = skey[q] != r;
+      if (!first) continue;
+      float v = o[r];
+      for (int q = k; q < K; ++q)
+        if (skey[q] == r) v -= val[(size_t)i * K + q];
+      o[r] = v;
+    }
+    __syncthreads();
+  } else if (t == 0) {
+    const int r = idx[(size_t)i * K];  // K == 1
+    if (r < 0 || (int64_t)r >= D) {
+      if (c == 0) {
+        atomicCAS(flags + F_ERR, 0, LST_EINDEX);
+        oc[i] = 0.0;
       }
+    } else if (r >= b && r < e) {
+      oc[i] = (double)o[r] + sh;
     }
   }
-  __syncthreads();
-  const bool shifted = loss_kind == LST_LOSS_SPHERICAL_SHIFTED;
-  const double sh = shifted ? (double)eps : 0.0;
   double acc = 0.0;
-  for (int64_t r = threadIdx.x; r < D; r += blockDim.x) {
-    const double u = (double)o[r] + sh;
-    acc += u * u;
+  for (int64_t r0 = b; r0 < e; r0 += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t r = r0 + 256 * u + t;
+      v[u] = o[r < e ? r : e - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double x = (double)v[u] + sh;
+      if (r0 + 256 * u + t < e) acc += x * x;
+    }
   }
-  red[threadIdx.x] = acc;
+  red[t] = acc;
   __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < (unsigned)off) red[threadIdx.x] += red[threadIdx.x + off];
+  for (int off = 128; off > 0; off >>= 1) {
+    if (t < off) red[t] += red[t + off];
     __syncthreads();
   }
-  const double sumsq = red[0];
+  if (t == 0) sums[(size_t)i * nch + c] = red[0];
+}
+
+// Chunk c of example i (squared error: one workgroup per example, which only
+// writes the loss).
+__global__ __launch_bounds__(256) void naive_finish_kernel(float* __restrict__ O, int64_t ldo,
+                                                           int64_t D, int nch,
+                                                           const int32_t* __restrict__ idx, int K,
+                                                           int loss_kind, float eps,
+                                                           const double* __restrict__ sums,
+                                                           const double* __restrict__ oc,
+                                                           float* __restrict__ loss, int* flags) {
+  const int c = blockIdx.x, i = blockIdx.y, t = threadIdx.x;
+  double sumsq = 0.0;
+  for (int q = 0; q < nch; ++q) sumsq += sums[(size_t)i * nch + q];
   if (loss_kind == LST_LOSS_SQUARED) {
-    if (threadIdx.x == 0) {
+    if (t == 0) {
       const float L = (float)sumsq;
       loss[i] = L;
       if (!isfinite(L)) atomicCAS(flags + F_ERR, 0, LST_ENONFINITE);
     }
     return;
   }
-  const int c = s_c;
+  const bool shifted = loss_kind == LST_LOSS_SPHERICAL_SHIFTED;
+  const double sh = shifted ? (double)eps : 0.0;
   const double S = shifted ? sumsq : sumsq + (double)D * eps;
-  const double oc = (c >= 0) ? (double)o[c] + sh : 0.0;
-  const double num = shifted ? oc * oc : oc * oc + eps;
+  const double o_c = oc[i];
+  const double num = shifted ? o_c * o_c : o_c * o_c + eps;
   const float a = (float)(2.0 / S);
-  const float b = shifted ? (float)(-2.0 / oc) : (float)(-2.0 * oc / num);
-  __syncthreads();  // every thread has read o[c] before it is rescaled
-  for (int64_t r = threadIdx.x; r < D; r += blockDim.x) o[r] = a * (float)((double)o[r] + sh);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (c >= 0) o[c] += b;
+  const float bc = shifted ? (float)(-2.0 / o_c) : (float)(-2.0 * o_c / num);
+  const int cls = idx[(size_t)i * K];  // matches no row when it is not one
+  int64_t b, e;
+  chunk_range(D, nch, c, b, e);
+  float* o = O + (size_t)i * ldo;
+  for (int64_t r0 = b; r0 < e; r0 += 8 * 256) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t r = r0 + 256 * u + t;
+      v[u] = o[r < e ? r : e - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t r = r0 + 256 * u + t;
+      const float x = a * (float)((double)v[u] + sh);
+      if (r < e) o[r] = r == cls ? x + bc : x;
+    }
+  }
+  if (c == 0 && t == 0) {
     const float L = (float)(-log(num) + log(S));
     loss[i] = L;
     if (!isfinite(L)) atomicCAS(flags + F_ERR, 0, LST_ENONFINITE);
@@ -305,9 +373,14 @@ __global__ __launch_bounds__(1024) void naive_rowstats_kernel(float* __restrict_
 
 hipError_t naive_rowstats(float* O, int64_t ldo, int64_t D, int m, const int32_t* idx,
                           const float* val, int K, int loss_kind, float eps, float* loss,
-                          int* flags, hipStream_t s) {
-  hipLaunchKernelGGL(naive_rowstats_kernel, dim3(m), dim3(1024), 0, s, O, ldo, D, idx, val, K,
-                     loss_kind, eps, loss, flags);
+                          double* ws, int* flags, hipStream_t s) {
+  const int nch = naive_chunks(D, m);
+  double* oc = ws + (size_t)m * nch;
+  hipLaunchKernelGGL(naive_chunk_kernel, dim3(nch, m), dim3(256), 0, s, O, ldo, D, nch, idx, val,
+                     K, loss_kind, eps, ws, oc, flags);
+  const int fin = loss_kind == LST_LOSS_SQUARED ? 1 : nch;
+  hipLaunchKernelGGL(naive_finish_kernel, dim3(fin, m), dim3(256), 0, s, O, ldo, D, nch, idx, K,
+                     loss_kind, eps, (const double*)ws, (const double*)oc, loss, flags);
   return hipGetLastError();
 }
 

@@ -218,6 +218,28 @@ def test_naive_path_small(gpu_lib):
         _assert(reports, W_rel, rows=False)
 
 
+@pytest.mark.parametrize("m,d,D", [(1, 4, 5), (1, 130, 1000), (31, 33, 700), (32, 128, 4096),
+                                   (33, 36, 129), (64, 96, 2051), (65, 260, 3000), (127, 127, 999),
+                                   (128, 129, 3001), (130, 500, 1025), (300, 64, 20000)])
+def test_naive_tile_edges(gpu_lib, m, d, D):
+    """The explicit-W products at the edges of their tiles (rows 32, 64, 128; columns 128; k
+    slices of 32), aligned and not, with repeated targets; the row sums in one chunk and in
+    many; the restore's product V U from the same shapes."""
+    cfg = _cfg(D=D, d=d, m=m, K=6, lr=1e-3, distinct=False, dup_frac=0.3, pad_frac=0.2,
+               entropy=700 + m + d)
+    reports, W_rel, _ = run_parity(cfg, 3, naive=True)
+    _assert(reports, W_rel, rows=False)
+    cfg = _cfg(D=D, d=d, m=m, K=1, lr=1e-3, loss="spherical", val_dist="one", entropy=800 + m + d)
+    reports, W_rel, _ = run_parity(cfg, 2, naive=True)
+    _assert(reports, W_rel, rows=False)
+    cfg = _cfg(D=D, d=d, m=min(m, 8), K=2, lr=1e-3, u_init="random", entropy=900 + m + d)
+    reports, W_rel, extra = run_parity(cfg, 1)
+    _assert(reports, W_rel)
+    extra["layer"].restore()
+    W = extra["layer"].materialize_W().cpu().numpy()
+    assert rel(W, extra["W_ref"]) < 1e-5
+
+
 @pytest.mark.timeout(600)
 def test_c2_paper_100_steps(gpu_lib):
     """D = 200000, d = 500, m = 128, K = 10, lr = 1e-3 at full size (the benchmarked
