@@ -268,7 +268,6 @@ hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if, con
   const int tmr = p.M <= 32 ? 32 : p.M <= 64 ? 64 : 128;
   p.tiles_m = (p.M + tmr - 1) / tmr;
   p.tiles_n = (p.N + kTN - 1) / kTN;
-  p.tile_begin = 0;
   const int total = p.tiles_m * p.tiles_n * (p.epi == EPI_PARTIAL ? p.ksplit : 1);
   if (total == 0) return hipSuccess;
   // 16-byte LDS-DMA: aligned rows, and whole pieces of a contiguous k

@@ -1,5 +1,5 @@
-// One output tile of the fp32 MFMA panel GEMM, as a device function shared by
-// the step kernel, plus the global-memory helpers of the large-product kernel.
+// One output tile of the fp32 MFMA panel GEMM, as a device function of the
+// step kernels, and the LDS-DMA helpers that the large products share.
 //
 // The products of the minibatch algorithm (Appendix A steps 1, 2, 4, 7, 8, 10)
 // are small (m = 16 .. 512 on one side, d = 32 .. 1024 on the others), so
@@ -48,25 +48,6 @@ __device__ __forceinline__ const float* vm_row(const VMat& v, int row) {
   int ld = v.ld[0], r0 = 0;
   if (v.nb > 1 && row >= v.r1) { base = v.p[1]; ld = v.ld[1]; r0 = v.r1; }
   return base + (size_t)(row - r0) * (size_t)ld;
-}
-
-__device__ __forceinline__ float4 vm_load4(const VMat& v, int row, int col, int nrows, int ncols) {
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (row >= nrows || col >= ncols) return o;
-  const float* base = vm_row(v, row);
-  if (v.vec && col + 3 < ncols) {
-    o = *reinterpret_cast<const float4*>(base + col);
-  } else {
-    o.x = base[col];
-    if (col + 1 < ncols) o.y = base[col + 1];
-    if (col + 2 < ncols) o.z = base[col + 2];
-    if (col + 3 < ncols) o.w = base[col + 3];
-  }
-  if (v.rscale) {
-    const float s = v.rscale[row];
-    o.x *= s; o.y *= s; o.z *= s; o.w *= s;
-  }
-  return o;
 }
 
 // ------------------------------------------------------------- LDS-DMA
@@ -230,9 +211,38 @@ __device__ __forceinline__ void fill_nk(const VMat& v, int o0, int nout, int k0,
   }
 }
 
+// Output index within the wave's tile edge of place x (0 .. 15) of block i: a
+// KC operand's blocks are 16 consecutive rows each; an NK operand's are
+// interleaved (IB x + i), so that one LDS read of IB consecutive floats feeds
+// the IB blocks of a lane (64-tiles: half the reads of a float each; both are
+// then free of bank conflicts).
+template <int T, int KC>
+__device__ __forceinline__ int blk_index(int i, int x) {
+  return KC ? i * 16 + x : PanelGeom<T>::IB * x + i;
+}
+
 // MFMA operand fragments of one 16-wide k slice: MFMA q of the slice pairs
 // k = kk + 4 g + q of A and of B (g = lane / 16), so a lane holds 4 values
-// of row/column l16 per 16 x 16 block.
+// of place l16 per 16 x 16 block.
+template <int T>
+__device__ __forceinline__ void load_frags_nk(const float* S, int w0, int kk,
+                                              float (&a)[PanelGeom<T>::IB][4]) {
+  constexpr int IB = PanelGeom<T>::IB;
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = w0 + IB * (lane & 15);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int k = kk + 4 * g + q;
+    const float* p = S + k * T + 4 * ((r >> 2) ^ swz_nk<T>(k)) + (r & 3);
+    if constexpr (IB == 2) {
+      const float2 f = *reinterpret_cast<const float2*>(p);
+      a[0][q] = f.x;
+      a[1][q] = f.y;
+    } else {
+      a[0][q] = *p;
+    }
+  }
+}
+
 template <int T, int AKC, int BKC>
 __device__ __forceinline__ void load_frags(const float* As, const float* Bs, int kk,
                                            float (&a)[PanelGeom<T>::IB][4],
@@ -242,35 +252,25 @@ __device__ __forceinline__ void load_frags(const float* As, const float* Bs, int
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int g = lane >> 4, l16 = lane & 15;
+  if (AKC) {
 #pragma unroll
-  for (int i = 0; i < IB; ++i) {
-    const int r = wm * G::WT + i * 16 + l16;
-    if (AKC) {
-      const int slot = (kk >> 2) + g;
+    for (int i = 0; i < IB; ++i) {
+      const int r = wm * G::WT + i * 16 + l16, slot = (kk >> 2) + g;
       const float4 f = *reinterpret_cast<const float4*>(As + r * G::CK + 4 * (slot ^ (r & 7)));
       a[i][0] = f.x; a[i][1] = f.y; a[i][2] = f.z; a[i][3] = f.w;
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = kk + 4 * g + q;
-        a[i][q] = As[k * T + 4 * ((r >> 2) ^ swz_nk<T>(k)) + (r & 3)];
-      }
     }
+  } else {
+    load_frags_nk<T>(As, wm * G::WT, kk, a);
   }
+  if (BKC) {
 #pragma unroll
-  for (int j = 0; j < IB; ++j) {
-    const int c = wn * G::WT + j * 16 + l16;
-    if (BKC) {
-      const int slot = (kk >> 2) + g;
+    for (int j = 0; j < IB; ++j) {
+      const int c = wn * G::WT + j * 16 + l16, slot = (kk >> 2) + g;
       const float4 f = *reinterpret_cast<const float4*>(Bs + c * G::CK + 4 * (slot ^ (c & 7)));
       b[j][0] = f.x; b[j][1] = f.y; b[j][2] = f.z; b[j][3] = f.w;
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = kk + 4 * g + q;
-        b[j][q] = Bs[k * T + 4 * ((c >> 2) ^ swz_nk<T>(k)) + (c & 3)];
-      }
     }
+  } else {
+    load_frags_nk<T>(Bs, wn * G::WT, kk, b);
   }
 }
 
@@ -434,8 +434,8 @@ __device__ __forceinline__ void panel_run(const GemmBatch& bt, const GemmProblem
     for (int j = 0; j < IB; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm * G::WT + i * 16 + 4 * (lane >> 4) + r;
-        const int col = n0 + wn * G::WT + j * 16 + (lane & 15);
+        const int row = m0 + wm * G::WT + blk_index<T, AKC>(i, 4 * (lane >> 4) + r);
+        const int col = n0 + wn * G::WT + blk_index<T, BKC>(j, lane & 15);
         pre1[i][j][r] = 0.f;
         pre2[i][j][r] = 0.f;
         if (row >= P.M || col >= P.N) continue;
@@ -539,7 +539,7 @@ __device__ __forceinline__ void panel_run(const GemmBatch& bt, const GemmProblem
     const float t = *X.s1;
     if (t > 0.f && isfinite(t)) pscale = ldexpf(1.f, max(-126, min(126, -2 * ilogbf(t))));
   }
-  // Element r of acc[i][j]: row 4*(lane/16) + r, column lane % 16 of its 16 x 16 block.
+  // Element r of acc[i][j]: place 4*(lane/16) + r by lane % 16 of its 16 x 16 block.
   float dsum[IB][4], asum[IB][4];
 #pragma unroll
   for (int i = 0; i < IB; ++i)
@@ -551,8 +551,8 @@ __device__ __forceinline__ void panel_run(const GemmBatch& bt, const GemmProblem
     for (int j = 0; j < IB; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm * G::WT + i * 16 + 4 * (lane >> 4) + r;
-        const int col = n0 + wn * G::WT + j * 16 + (lane & 15);
+        const int row = m0 + wm * G::WT + blk_index<T, AKC>(i, 4 * (lane >> 4) + r);
+        const int col = n0 + wn * G::WT + blk_index<T, BKC>(j, lane & 15);
         if (row >= P.M || col >= P.N) continue;
         const float v = acc[i][j][r];
         if (epi_is<EPIS>(P, EPI_STORE)) {
@@ -606,7 +606,7 @@ __device__ __forceinline__ void panel_run(const GemmBatch& bt, const GemmProblem
         v += __shfl_xor(v, 2);
         v += __shfl_xor(v, 4);
         v += __shfl_xor(v, 8);
-        const int row = m0 + wm * G::WT + i * 16 + 4 * (lane >> 4) + r;
+        const int row = m0 + wm * G::WT + blk_index<T, AKC>(i, 4 * (lane >> 4) + r);
         if ((lane & 15) == 0 && row < P.M) X.dotp[(size_t)row * X.ld_dotp + 2 * tn + wn] = v;
       }
   }
@@ -621,7 +621,7 @@ __device__ __forceinline__ void panel_run(const GemmBatch& bt, const GemmProblem
         v += __shfl_xor(v, 2);
         v += __shfl_xor(v, 4);
         v += __shfl_xor(v, 8);
-        const int row = m0 + wm * G::WT + i * 16 + 4 * (lane >> 4) + r;
+        const int row = m0 + wm * G::WT + blk_index<T, AKC>(i, 4 * (lane >> 4) + r);
         if ((lane & 15) == 0 && row < P.M) X.absp[(size_t)row * X.ld_absp + pc] = v;
       }
   }
@@ -655,18 +655,30 @@ enum : unsigned { TILE32 = 1, TILE64 = 2 };
 
 // Computes the tile of block t of the batch (problems laid out one after
 // another, each in column-panel-major order); smem holds bt.stages stages of
-// kPanelStageBytes.  Only the tile edges in TILES, the layouts in VARS and the
+// kPanelStageBytes.  An XCD takes one contiguous run of the whole tile
+// sequence, or with SHARES of every problem's tiles an eighth (rounded up):
+// with problems of several K the first gives some XCDs only the long tiles.
+// D = 500 000, d = 1024, m = 512: step 249 -> 240 us with SHARES; d = 512, m =
+// 256: 90.2 -> 88.6; d = 500, m = 128 (tiles of 6 to 9 us): 40.1 -> 40.6, so not
+// there.  Only the tile edges in TILES, the layouts in VARS and the
 // epilogues in EPIS are compiled (the host checks every problem).
-template <unsigned TILES, int W, unsigned VARS, unsigned EPIS>
+template <unsigned TILES, int W, unsigned VARS, unsigned EPIS, bool SHARES>
 __device__ __forceinline__ void panel_tile(const GemmBatch& bt, int t, float* smem) {
-  t = xcd_tile(t, bt.total_tiles);
   int q = 0;
-  while (q + 1 < bt.np && t >= bt.tile_begins[q + 1]) ++q;
+  if (SHARES) {
+    const int li = t >> 3;
+    while (q + 1 < bt.np && li >= bt.tile_begins[q + 1]) ++q;
+    t = (t & 7) * (bt.tile_begins[q + 1] - bt.tile_begins[q]) + li - bt.tile_begins[q];
+  } else {
+    t = xcd_tile(t, bt.total_tiles);
+    while (q + 1 < bt.np && t >= bt.tile_begins[q + 1]) ++q;
+  }
   if (bt.skip_updates_if && q >= bt.first_update && *bt.skip_updates_if) return;
   // A private copy: the inline-asm memory clobbers of the pipeline would
   // otherwise make every use re-read the descriptor from kernel arguments.
   const GemmProblem P = bt.p[q];
-  int lt = t - P.tile_begin;
+  int lt = SHARES ? t : t - P.tile_begin;
+  if (SHARES && lt >= P.ntiles) return;  // past the end of an XCD's rounded-up share
   int tm, tn, kb = 0, ke = P.K, z = 0;
   if (epi_is<EPIS>(P, EPI_SYM)) {
     int TT = P.tiles_m, r = 0;

@@ -653,6 +653,11 @@ int enqueue_step(lst_state* s, hipStream_t st, int32_t m, int32_t K, const float
       g.np = 2;  // no U^{-T}
       L.ntask = 1;
     }
+    // 64 x 64 tiles for Q too (half the LDS reads, a quarter of the blocks) when
+    // the tiles of all problems then still are two a compute unit.  d = 1024, m =
+    // 512 (648 tiles): 240 -> 238 us; d = 512, m = 256 (164): 88.6 -> 95, not there.
+    const int t64 = (d + 63) / 64;
+    if (m > 128 && t64 * (t64 + 1) / 2 + (g.np - 1) * t64 * t64 >= kManyTiles) g.p[0].tile = 64;
     OK_OR_RETURN(run_launch(s, c, L, stages_for(g, launch34_stages(g)), st, PH_LAUNCH4));
     if (scratch) {
       StepLaunch C{};

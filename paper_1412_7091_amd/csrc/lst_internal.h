@@ -67,6 +67,7 @@ struct alignas(64) GemmProblem {  // whole kernel-argument cache lines each
   int tile;         // step GEMMs: output tile edge, 32 or 64 (0: 32)
   int tiles_m, tiles_n, tile_begin;
   int ct_off;       // EPI_STORE_T: offset of the transpose from C
+  int ntiles;
   VMat A, B;
   float* C;
 };
@@ -102,6 +103,7 @@ struct GemmBatch {
   int np;
   int total_tiles;
   int tile_begins[kMaxProblems + 1];  // first tile of each problem; [np] = total_tiles
+                                      // (launches in shares: both within one XCD's eighth)
   int stages;                  // LDS stages of the K pipeline (>= 2)
   int timing_slot;             // record of per-block phase times (builds with LST_TIMING only)
   int first_update;

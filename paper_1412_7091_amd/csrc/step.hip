@@ -2075,6 +2075,9 @@ constexpr LaunchMasks launch_masks(int lk, bool small) {
   return M;
 }
 
+// Launches whose tiles go to the XCDs in shares of every problem (panel_tile).
+constexpr bool launch_shares(int lk, bool small) { return !small && (lk == 4 || lk == 7); }
+
 template <bool SMALLM, int W, int LK>
 __device__ __forceinline__ void run_task(const StepCtx& c, const StepLaunch& L, int t, int local,
                                          unsigned char* sraw) {
@@ -2085,7 +2088,8 @@ __device__ __forceinline__ void run_task(const StepCtx& c, const StepLaunch& L, 
       if constexpr (!((M.epis >> EPX_LATE_SKIP) & 1u)) {
         if (L.gemm.skip_if && *L.gemm.skip_if) return;
       }
-      panel_tile<M.tiles, W, M.vars, M.epis>(L.gemm, local, reinterpret_cast<float*>(sraw));
+      panel_tile<M.tiles, W, M.vars, M.epis, launch_shares(LK, SMALLM)>(
+          L.gemm, local, reinterpret_cast<float*>(sraw));
       return;
     }
   }
@@ -2144,7 +2148,7 @@ void step_kernel(StepCtx c, StepLaunch L) {
     // kind | GEMM problem + 1 << 4 | HW_ID << 8 | XCC_ID << 40
     unsigned long long tag = (unsigned long long)L.kind[t];
     if (L.kind[t] == TK_GEMM) {
-      const int tt = xcd_tile(local, L.gemm.total_tiles);
+      const int tt = launch_shares(LK, SMALLM) ? local >> 3 : xcd_tile(local, L.gemm.total_tiles);
       int q = 0;
       while (q + 1 < L.gemm.np && tt >= L.gemm.tile_begins[q + 1]) ++q;
       tag |= (unsigned long long)(q + 1) << 4;
@@ -2169,7 +2173,7 @@ static size_t lds_of(int kind, int stages, int m, int K) {
   }
 }
 
-static int tiles_of(GemmBatch& b) {
+static int tiles_of(GemmBatch& b, bool shares) {
   int total = 0;
   for (int q = 0; q < b.np; ++q) {
     GemmProblem& p = b.p[q];
@@ -2179,14 +2183,14 @@ static int tiles_of(GemmBatch& b) {
     p.tile_begin = total;
     b.tile_begins[q] = total;
     if (p.ksplit < 1) p.ksplit = 1;
-    if (p.epi == EPI_SYM)
-      total += p.tiles_m * (p.tiles_m + 1) / 2;
-    else
-      total += p.tiles_m * p.tiles_n * (p.epi == EPI_PARTIAL ? p.ksplit : 1);
+    p.ntiles = p.epi == EPI_SYM
+                   ? p.tiles_m * (p.tiles_m + 1) / 2
+                   : p.tiles_m * p.tiles_n * (p.epi == EPI_PARTIAL ? p.ksplit : 1);
+    total += shares ? (p.ntiles + 7) / 8 : p.ntiles;
   }
-  b.total_tiles = total;
   b.tile_begins[b.np] = total;
-  return total;
+  b.total_tiles = shares ? 8 * total : total;
+  return b.total_tiles;
 }
 
 int step_task_blocks(int kind, const StepCtx& c) {
@@ -2226,9 +2230,9 @@ static const void* kfn() {
 // The kernel built for (launch kind, m <= 128, 16-byte DMA); nullptr for a
 // combination that is not built.
 // Launch kinds with a kernel of their own for m > 128 (64 x 64 tiles, the
-// solve's memory-streamed iterations, the T product from N); the others run
-// the m <= 128 kernel at every m.
-constexpr bool has_large_kernel(int lk) { return lk == 1 || lk == 2 || lk == 3 || lk == 6; }
+// solve's memory-streamed iterations, the T product from N, launch 4's tiles in
+// shares); the others run the m <= 128 kernel at every m.
+constexpr bool has_large_kernel(int lk) { return lk != 5; }
 
 static const void* step_kernel_for(int lk, bool small, int w16) {
   switch (lk) {
@@ -2241,12 +2245,16 @@ static const void* step_kernel_for(int lk, bool small, int w16) {
     case 3:
       if (small) return w16 ? kfn<true, 4, 3>() : kfn<true, 1, 3>();
       return w16 ? kfn<false, 4, 3>() : kfn<false, 1, 3>();
-    case 4: return w16 ? kfn<true, 4, 4>() : kfn<true, 1, 4>();
+    case 4:
+      if (small) return w16 ? kfn<true, 4, 4>() : kfn<true, 1, 4>();
+      return w16 ? kfn<false, 4, 4>() : kfn<false, 1, 4>();
     case 5: return w16 ? kfn<true, 4, 5>() : kfn<true, 1, 5>();
     case 6:
       if (small) return w16 ? kfn<true, 4, 6>() : kfn<true, 1, 6>();
       return w16 ? kfn<false, 4, 6>() : kfn<false, 1, 6>();
-    case 7: return w16 ? kfn<true, 4, 7>() : kfn<true, 1, 7>();
+    case 7:
+      if (small) return w16 ? kfn<true, 4, 7>() : kfn<true, 1, 7>();
+      return w16 ? kfn<false, 4, 7>() : kfn<false, 1, 7>();
     default: return nullptr;
   }
 }
@@ -2323,7 +2331,7 @@ hipError_t step_launch(const StepCtx& c, StepLaunch& L, int stages, hipStream_t 
             (rowsums && (p.epi != EPI_STORE || !((M.epis >> EPX_ROWSUMS) & 1u))))
           return hipErrorInvalidValue;
       }
-      n = tiles_of(L.gemm);
+      n = tiles_of(L.gemm, launch_shares(L.lk, small));
       w16 = gemm_batch_vec16(L.gemm);
     } else {
       n = step_task_blocks(L.kind[t], c);

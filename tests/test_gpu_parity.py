@@ -218,6 +218,21 @@ def test_naive_path_small(gpu_lib):
         _assert(reports, W_rel, rows=False)
 
 
+@pytest.mark.parametrize("m,d", [(129, 33), (129, 130), (200, 512), (150, 1001), (140, 1100)])
+def test_wide_minibatch_update_tiles(gpu_lib, m, d):
+    """Launch 4 for m > 128: each XCD's share of every product's tiles, fewer tiles than XCDs
+    and shares that end inside the last one, and from d = 897 on 64 x 64 tiles for Q (aligned
+    rows and not), with Q, U and U^{-T} against W and each other."""
+    cfg = _cfg(D=2500, d=d, m=m, K=3, lr=1e-3, entropy=1000 + m + d)
+    reports, W_rel, extra = run_parity(cfg, 3)
+    _assert(reports, W_rel)
+    Q, U, Uit = (x.cpu().numpy().astype(np.float64) for x in extra["layer"].get_state())
+    W = extra["W_ref"]
+    assert np.array_equal(Q, Q.T)
+    assert rel(Q, W.T @ W) < 1e-5
+    assert rel(U @ Uit.T, np.eye(d)) < 1e-5
+
+
 @pytest.mark.parametrize("m,d,D", [(1, 4, 5), (1, 130, 1000), (31, 33, 700), (32, 128, 4096),
                                    (33, 36, 129), (64, 96, 2051), (65, 260, 3000), (127, 127, 999),
                                    (128, 129, 3001), (130, 500, 1025), (300, 64, 20000)])
