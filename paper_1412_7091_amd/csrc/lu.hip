@@ -12,17 +12,20 @@
 // and every access to a row goes through one of the two.  Launch p applies
 // panel p - 1 to everything on its right and factors panel p:
 //   block 0        the columns of panel p: U12 by substitution, the rank-32
-//                  update on MFMA, then the panel itself with one active row
-//                  per thread (registers);
+//                  update on MFMA into LDS, then the panel itself;
 //   blocks 1 ..    32 columns each of the panels after p: U12 and the update;
 //   last block     inverses of the 16 x 16 diagonal blocks of panel p - 1 for
 //                  the row solves.
-// Factoring a panel is a chain of 32 links.  A link: the largest |a| of the
-// column per wave (DPP, no LDS), its row published in LDS by the lane that
-// holds it, one barrier, the wave holding the largest found by every wave for
-// itself, the row read back as a broadcast, the rank-1 update.  The column in
-// hand is always register 0 (the update shifts the row by one register), so
-// a link is one loop body.
+// Factoring a panel is a chain of 32 links.  Up to 512 active rows four waves
+// take eight columns each, all rows in the registers of each (WavePanel): a
+// link is then one wave's arg-max by DPP, its row by v_readlane and the rank-1
+// update, without a barrier, and the waves on its right catch up meanwhile.
+// Above, a row per thread on all waves (panel_links), because eight columns of
+// 1024 rows do not fit a wave's registers: a link is the largest |a| per wave,
+// its row published in LDS, one barrier, the wave holding the largest found by
+// every wave for itself, the row read back, the update.  In both the column in
+// hand is always register 0 (the update shifts the row by one register), so a
+// link is one loop body.
 //
 // Row solves, P A = L R: A z = h is z = R^{-1} L^{-1} P h.  A workgroup solves
 // for 16 examples; its waves hold the right-hand sides as MFMA accumulators
@@ -33,11 +36,15 @@
 // subtracts the block's part from the blocks it owns, the factor's fragments
 // loaded several links ahead.
 //
-// At d = 500, m = 128: 480 us for the factorisation (16 launches of 25 to 34
-// us, a link about 0.75 us; 1.4 ms when a link was three barriers and ten
-// shuffles and the interchanges and the update were launches of their own)
-// and 47 us for the solves (0.5 ms with a launch per 64 unknowns on m / 16
-// workgroups).
+// At d = 500, m = 128: 440 us for the factorisation and 47 us for the solves
+// (1.4 ms when a link was three barriers and ten shuffles and the interchanges
+// and the update were launches of their own; 0.5 ms for the solves with a
+// launch per 64 unknowns on m / 16 workgroups).  The 16 panel launches take 34
+// us (500 rows) down to 17, of which the update's loads and substitution are
+// 9 to 4 us and the links the rest: 0.7 us each at 500 rows (7 columns of 8
+// rows per lane to update, in one wave), 0.25 at 32.  With panel_links for all
+// sizes a link was 0.75 us and the step 585 us instead of 553 (d = 256: 304
+// instead of 279; d = 1024, whose first half keeps them: 1506 and 1459).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -57,12 +64,20 @@ constexpr int kRB = 4;         // 16-row blocks of a wave in the rank-32 update
 // updated columns on their way from MFMA layout to a row per thread, then the
 // multipliers), and the small blocks.
 struct PanelSmall {
-  float L11[kNB][kLdT];        // multipliers of the previous panel's pivot rows
+  float L11[kNB][kLdT];        // multipliers of pivot rows, by column: L11[k][i] = l_ik
   float U12T[kNB][kLdT];       // U12, a row per column
   float slot[2][16][kLdT];     // each wave's candidate row (by parity of the link)
   unsigned skey[2][16];
   int prow[kNB];               // rows of the previous panel's pivots
   int wcnt[16];
+  // panels of up to 512 rows
+  float U[kNB][kNB];           // rows of R right of the pivot's eight columns
+  float Ud[kNB][8];            // and within them, from the pivot on
+  int pslot[kNB];              // active row chosen at each link
+  volatile int done;           // links whose multipliers are in T
+  int rowid[512];              // the active rows
+  short step[512];             // link that chose each active row (kNB: none)
+  int bad;                     // a pivot was zero or not finite
 };
 __host__ __device__ inline size_t panel_lds_bytes(int nt) {
   return (size_t)kNB * (nt + 4) * sizeof(float) + sizeof(PanelSmall);
@@ -141,6 +156,51 @@ __device__ void diag_inverses(const LuArgs& a, int q0, PanelSmall& sm) {
   }
 }
 
+// y <- L^{-1} y (16 entries at yp, a lane's own) for the unit lower triangle
+// with column k at Lc + kLdT k: each entry is subtracted from all later ones as
+// it becomes final, so that the only chain is one multiply-add an entry (a dot
+// product per entry is a chain of them).
+__device__ __forceinline__ void substitute16(const float* Lc, float* yp) {
+  float y[16];
+#pragma unroll
+  for (int i = 0; i < 16; i += 4) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(yp + i);
+    y[i] = v[0]; y[i + 1] = v[1]; y[i + 2] = v[2]; y[i + 3] = v[3];
+  }
+#pragma unroll
+  for (int k = 0; k < 15; ++k) {
+#pragma unroll
+    for (int i = (k + 1) / 4 * 4; i < 16; i += 4) {
+      const floatx4 l = *reinterpret_cast<const floatx4*>(Lc + k * kLdT + i);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i + q > k) y[i + q] -= l[q] * y[k];
+    }
+    // (or all of L is read into registers first)
+    if (k % 4 == 3) asm volatile("" ::: "memory");
+  }
+#pragma unroll
+  for (int i = 0; i < 16; i += 4)
+    *reinterpret_cast<floatx4*>(yp + i) = floatx4{y[i], y[i + 1], y[i + 2], y[i + 3]};
+}
+
+// The same for 32 entries: the first 16, their part in the others, the others.
+__device__ __forceinline__ void substitute32(const float (*L)[kLdT], float* yp) {
+  substitute16(&L[0][0], yp);
+  floatx4 y[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) y[i] = *reinterpret_cast<const floatx4*>(yp + 16 + 4 * i);
+#pragma unroll 4
+  for (int k = 0; k < 16; ++k) {
+    const float yk = yp[k];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] -= *reinterpret_cast<const floatx4*>(&L[k][16 + 4 * i]) * yk;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) *reinterpret_cast<floatx4*>(yp + 16 + 4 * i) = y[i];
+  substitute16(&L[16][16], yp + 16);
+}
+
 // Columns s0 .. s0 + 31 (as far as they go): U12 = L11^{-1} A[pivots] of the
 // panel at column q0 = j0 - 32, written back, then A[active] -= L21 U12.  The
 // result stays in LDS (T[column][active row]) or goes back to memory.
@@ -162,15 +222,15 @@ __device__ __forceinline__ void update_columns(const LuArgs& a, int s0, float* T
     for (int r = 0; r < 4; ++r) crow[t][r] = a.act[min(b + 4 * g + r, R - 1)];
   }
   __syncthreads();
-  // L11 and the slab's pivot rows: thread (i, c) of 32 x 32 (NT >= 256)
-  {
-    const int c = tid & 31;
-    for (int i = tid >> 5; i < kNB; i += NT / 32) {
-      const float* row = a.A + (size_t)sm.prow[i] * d;
-      const float lv = row[q0 + c], uv = row[s0 + min(c, nc - 1)];
-      sm.L11[i][c] = lv;
-      sm.U12T[c][i] = uv;
-    }
+  // L11 and the slab's pivot rows: thread (i, c) of 32 x 32, NT / 32 rows at a
+  // time, every load issued before the first is used
+  constexpr int kPer = kNB * kNB / NT;
+  float lv[kPer], uv[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const float* row = a.A + (size_t)sm.prow[(tid >> 5) + u * (NT / 32)] * d;
+    lv[u] = row[q0 + (tid & 31)];
+    uv[u] = row[s0 + min(tid & 31, nc - 1)];
   }
   // The update's operands are requested before the substitution and used after
   // it, except by 1024 threads, whose 128 registers do not hold them so long.
@@ -190,31 +250,14 @@ __device__ __forceinline__ void update_columns(const LuArgs& a, int s0, float* T
   if (NT < 1024)
 #pragma unroll
     for (int t = 0; t < kRB; ++t) operands(t);
-  __syncthreads();
-  if (tid < kNB) {  // a column per lane
-    float x[kNB];
 #pragma unroll
-    for (int i = 0; i < kNB; i += 4) {
-      const floatx4 v = *reinterpret_cast<const floatx4*>(&sm.U12T[tid][i]);
-      x[i] = v[0]; x[i + 1] = v[1]; x[i + 2] = v[2]; x[i + 3] = v[3];
-    }
-#pragma unroll
-    for (int i = 1; i < kNB; ++i) {
-      float s0v = x[i], s1v = 0.f;
-#pragma unroll
-      for (int k = 0; k < i; k += 4) {
-        const floatx4 l = *reinterpret_cast<const floatx4*>(&sm.L11[i][k]);
-        s0v -= l[0] * x[k];
-        if (k + 1 < i) s1v -= l[1] * x[k + 1];
-        if (k + 2 < i) s0v -= l[2] * x[k + 2];
-        if (k + 3 < i) s1v -= l[3] * x[k + 3];
-      }
-      x[i] = s0v + s1v;
-    }
-#pragma unroll
-    for (int i = 0; i < kNB; i += 4)
-      *reinterpret_cast<floatx4*>(&sm.U12T[tid][i]) = floatx4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+  for (int u = 0; u < kPer; ++u) {
+    const int i = (tid >> 5) + u * (NT / 32), c = tid & 31;
+    sm.L11[c][i] = lv[u];
+    sm.U12T[c][i] = uv[u];
   }
+  __syncthreads();
+  if (tid < kNB) substitute32(sm.L11, sm.U12T[tid]);  // a column per lane
   __syncthreads();
   {
     const int c = tid & 31;
@@ -315,38 +358,151 @@ __device__ __forceinline__ void panel_links(float (&x)[kNB], int c0, int nc, boo
   }
 }
 
-template <int NT, bool VEC>
-__global__ __launch_bounds__(NT) void lu_panel_kernel(LuArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  constexpr int NW = NT / 64, TLD = NT + 4;
-  float* T = reinterpret_cast<float*>(lds_raw);
-  PanelSmall& sm = *reinterpret_cast<PanelSmall*>(lds_raw + (size_t)kNB * TLD * sizeof(float));
+// ------------------------------------------------ panels of up to 512 rows
+// Four waves, eight columns each, with rows 64 r + lane in their registers.  A
+// wave first follows: as a link's multipliers appear in T it takes its own part
+// of the pivot row by v_readlane and applies the rank-1 update.  When all
+// earlier links are done it leads: largest |a| by DPP, its row by ballots, the
+// multipliers into T, one link after another with no barrier and no LDS round
+// trip between them.  The update of a link thus runs on four SIMDs, and only
+// the leader's eight columns of it lie in the chain.
+template <int RPL>
+struct WavePanel {
+  float x[RPL][8];
+  int ret[RPL];   // 0x80000000 once the row is chosen (or does not exist), else 0
+  int step[RPL];  // the link that chose it
+  float p[8];     // the pivot row
+
+  // Active row 64 r + src is the pivot of link c: its entries into p and to
+  // out, and retired.
+  template <int r>
+  __device__ __forceinline__ void retire(int src, int c, float* out) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      p[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[r][i]), src));
+    if ((int)(threadIdx.x & 63) == src) {
+      ret[r] = (int)0x80000000;
+      step[r] = c;
+#pragma unroll
+      for (int i = 0; i < 8; i += 4)
+        *reinterpret_cast<floatx4*>(out + i) =
+            floatx4{x[r][i], x[r][i + 1], x[r][i + 2], x[r][i + 3]};
+    }
+    // keeps the branches of different r apart (merged, they would index the
+    // registers by r)
+    asm volatile("; row %0" ::"n"(r));
+  }
+  // Row r or a later one holds the largest key.
+  template <int r>
+  __device__ __forceinline__ void choose(const int (&key)[RPL], int wm, int c, PanelSmall& sm) {
+    if constexpr (r < RPL) {
+      const unsigned long long mk = __ballot(key[r] == wm);
+      if (mk != 0ull || r == RPL - 1) {
+        const int src = mk != 0ull ? __ffsll((unsigned long long)mk) - 1 : 0;
+        retire<r>(src, c, sm.Ud[c]);
+        if ((threadIdx.x & 63) == 0) sm.pslot[c] = 64 * r + src;
+      } else {
+        choose<r + 1>(key, wm, c, sm);
+      }
+    }
+  }
+  template <int r>
+  __device__ __forceinline__ void take(int slot, int c, float* out) {
+    if constexpr (r < RPL) {
+      if ((slot >> 6) == r || r == RPL - 1)
+        retire<r>(slot & 63, c, out);
+      else
+        take<r + 1>(slot, c, out);
+    }
+  }
+
+  __device__ __forceinline__ void run(int w, int R, int nc, float* T, int tld, PanelSmall& sm) {
+    const int lane = threadIdx.x & 63, cb = 8 * w;
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+      ret[r] = 64 * r + lane < R ? 0 : (int)0x80000000;
+      step[r] = kNB;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[r][i] = T[(cb + i) * tld + 64 * r + lane];
+    }
+    for (int c = 0; c < cb; ++c) {
+      while (sm.done <= c) __builtin_amdgcn_s_sleep(1);  // a leader always gets there
+      asm volatile("" ::: "memory");
+      const int slot = __builtin_amdgcn_readfirstlane(sm.pslot[c]);
+      float l[RPL];
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) l[r] = T[c * tld + 64 * r + lane];
+      take<0>(slot, c, &sm.U[c][cb]);
+#pragma unroll
+      for (int r = 0; r < RPL; ++r)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[r][i] -= l[r] * p[i];
+    }
+    // lead: the column of the link is x[.][0], the rows shift as they are updated
+    for (int s = 0; s < 8; ++s) {
+      const int c = cb + s;
+      if (c >= nc) break;
+      // |a| as an integer orders like |a| (a NaN above infinity); chosen rows
+      // are negative
+      int key[RPL], km = (int)0x80000000;
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) {
+        key[r] = (__float_as_int(x[r][0]) & 0x7fffffff) | ret[r];
+        km = max(km, key[r]);
+      }
+      km = max(km, __builtin_amdgcn_update_dpp(0, km, 0x128, 0xf, 0xf, false));
+      km = max(km, __builtin_amdgcn_update_dpp(0, km, 0x124, 0xf, 0xf, false));
+      km = max(km, __builtin_amdgcn_update_dpp(0, km, 0x122, 0xf, 0xf, false));
+      km = max(km, __builtin_amdgcn_update_dpp(0, km, 0x121, 0xf, 0xf, false));
+      const int wm = max(max(__builtin_amdgcn_readlane(km, 0), __builtin_amdgcn_readlane(km, 16)),
+                         max(__builtin_amdgcn_readlane(km, 32), __builtin_amdgcn_readlane(km, 48)));
+      choose<0>(key, wm, c, sm);
+      if (lane == 0 && (!(fabsf(p[0]) > 0.f) || !isfinite(p[0]))) sm.bad = 1;
+      const float rc = 1.f / p[0];
+      float l[RPL];
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) {
+        l[r] = ret[r] == 0 ? x[r][0] * rc : 0.f;
+        T[c * tld + 64 * r + lane] = l[r];
+      }
+      // published after the multipliers and pslot (a wave's LDS accesses
+      // complete in order)
+      asm volatile("" ::: "memory");
+      if (lane == 0) sm.done = c + 1;
+#pragma unroll
+      for (int r = 0; r < RPL; ++r)
+#pragma unroll
+        for (int i = 0; i < 7; ++i) x[r][i] = x[r][i + 1] - l[r] * p[i + 1];
+    }
+    if (w == (nc - 1) / 8) {  // it has seen every link
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) sm.step[64 * r + lane] = (short)step[r];
+    }
+  }
+};
+
+// The panel's columns in T, active rows 0 .. R - 1 (R <= 64 RPL).
+template <int RPL>
+__device__ __forceinline__ void factor_by_waves(float* T, int tld, int R, int nc, PanelSmall& sm) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (8 * w < nc) {  // waves 0 .. 3
+    WavePanel<RPL> wp;
+    wp.run(w, R, nc, T, tld, sm);
+  }
+}
+
+// Links of a panel of more than 512 rows: a row per thread, all waves.
+template <int NT>
+__device__ __forceinline__ void factor_by_block(const LuArgs& a, float* T, int R, int nc, int row,
+                                                bool& active, PanelSmall& sm) {
+  constexpr int TLD = NT + 4;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int d = a.d, R = d - a.j0, nc = min(kNB, R);
-  if (blockIdx.x > 0) {
-    const int s0 = a.j0 + kNB * (int)blockIdx.x;
-    if (s0 < d)
-      update_columns<NT, VEC, false>(a, s0, T, sm);
-    else if (w == 0)
-      diag_inverses(a, a.j0 - kNB, sm);
-    return;
-  }
   float x[kNB];
-  bool active = tid < R;
-  const int row = a.act[min(tid, R - 1)];
-  if (a.j0 > 0) {
-    update_columns<NT, VEC, true>(a, a.j0, T, sm);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kNB; ++c) x[c] = T[c * TLD + tid];
-  } else {
-    const float* rp = a.A + (size_t)row * d;
-#pragma unroll
-    for (int c = 0; c < kNB; ++c) x[c] = rp[min(c, nc - 1)];
-  }
   // (threads past the rows and columns past the panel hold values that are
   // never used: a row that is not active takes no part, a column past the end
   // is not reached)
+#pragma unroll
+  for (int c = 0; c < kNB; ++c) x[c] = T[c * TLD + tid];
   int step = kNB;  // the link that chose this row
   // a wave writes T only at its own rows, which only it has read
   panel_links<NT, 32>(x, 0, nc, active, step, row, a, T, sm);
@@ -358,7 +514,80 @@ __global__ __launch_bounds__(NT) void lu_panel_kernel(LuArgs a) {
     const int src = r0 + (lane >> 5), c = lane & 31;
     const int rr = __shfl(row, src), st = __shfl(step, src);
     const int t = 64 * w + src;
-    if (t < R && c < nc && c < st) a.A[(size_t)rr * d + a.j0 + c] = T[c * TLD + t];
+    if (t < R && c < nc && c < st) a.A[(size_t)rr * a.d + a.j0 + c] = T[c * TLD + t];
+  }
+}
+
+template <int NT, bool VEC>
+__global__ __launch_bounds__(NT) void lu_panel_kernel(LuArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  constexpr int NW = NT / 64, TLD = NT + 4;
+  float* T = reinterpret_cast<float*>(lds_raw);
+  PanelSmall& sm = *reinterpret_cast<PanelSmall*>(lds_raw + (size_t)kNB * TLD * sizeof(float));
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int d = a.d, R = d - a.j0, nc = min(kNB, R);
+  if (blockIdx.x > 0) {
+    const int s0 = a.j0 + kNB * (int)blockIdx.x;
+    if (s0 < d)
+      update_columns<NT, VEC, false>(a, s0, T, sm);
+    else if (w == 0)
+      diag_inverses(a, a.j0 - kNB, sm);
+    return;
+  }
+  bool active = tid < R;
+  const int row = a.act[min(tid, R - 1)];
+  if (NT < 1024) sm.rowid[tid & 511] = row;
+  if (tid == 0) {
+    sm.done = 0;
+    sm.bad = 0;
+  }
+  if (a.j0 > 0) {
+    update_columns<NT, VEC, true>(a, a.j0, T, sm);
+  } else {
+    // 32 lanes a row
+    for (int t = tid >> 5; t < R; t += NT / 32)
+      T[(tid & 31) * TLD + t] = a.A[(size_t)a.act[t] * d + min(tid & 31, nc - 1)];
+  }
+  __syncthreads();
+  if constexpr (NT == 1024) {
+    factor_by_block<NT>(a, T, R, nc, row, active, sm);
+  } else {
+    const int rpl = (R + 63) / 64;  // 1 .. NT / 64
+    switch (rpl) {
+      case 1: factor_by_waves<1>(T, TLD, R, nc, sm); break;
+      case 2: factor_by_waves<2>(T, TLD, R, nc, sm); break;
+      case 3: factor_by_waves<3>(T, TLD, R, nc, sm); break;
+      case 4: factor_by_waves<4>(T, TLD, R, nc, sm); break;
+      default:
+        if constexpr (NT == 512) {
+          if (rpl == 5) factor_by_waves<5>(T, TLD, R, nc, sm);
+          else if (rpl == 6) factor_by_waves<6>(T, TLD, R, nc, sm);
+          else if (rpl == 7) factor_by_waves<7>(T, TLD, R, nc, sm);
+          else factor_by_waves<8>(T, TLD, R, nc, sm);
+        }
+        break;
+    }
+    __syncthreads();
+    // everything goes back: multipliers before the link that chose the row,
+    // the row of R from there on
+    {
+      const int c = tid & 31;
+#pragma unroll 4
+      for (int t = tid >> 5; t < R; t += NT / 32) {
+        const int st = sm.step[t];
+        const float* src = c < st                  ? T + c * TLD + t
+                           : (c >> 3) == (st >> 3) ? &sm.Ud[st][c - st]
+                                                   : &sm.U[st][c];
+        const float v = *src;
+        if (c < nc) a.A[(size_t)sm.rowid[t] * d + a.j0 + c] = v;
+      }
+    }
+    if (tid < R) {
+      const int st = sm.step[tid];
+      active = st == kNB;
+      if (!active) a.piv[a.j0 + st] = row;
+    }
+    if (tid == 0 && sm.bad) atomicCAS(a.flags + F_ERR, 0, LST_ESINGULAR);
   }
   // the rows that stay active, in order
   const unsigned long long on = __ballot(active);
@@ -367,7 +596,9 @@ __global__ __launch_bounds__(NT) void lu_panel_kernel(LuArgs a) {
   int off = __popcll(on & ((1ull << lane) - 1ull));
   for (int v = 0; v < w; ++v) off += sm.wcnt[v];
   if (active) a.act_next[off] = row;
-  if (R <= kNB && w == 0) diag_inverses(a, a.j0, sm);  // the last panel (in the wave that wrote it)
+  // the last panel's own diagonal blocks (after the barrier above, which
+  // follows the block's stores to A and piv)
+  if (R <= kNB && w == 0) diag_inverses(a, a.j0, sm);
 }
 
 __global__ __launch_bounds__(256) void lu_iota_kernel(int* act, int d) {
