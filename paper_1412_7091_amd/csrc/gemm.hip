@@ -327,14 +327,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* ws, int
 
 static int aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
-VMat vmat(const float* p, int ld, int rows, const float* rscale) {
+VMat vmat(const float* p, int ld, int rows) {
   VMat v{};
   v.p[0] = p;
   v.ld[0] = ld;
   v.r1 = rows;
   v.nb = 1;
   v.vec = (ld % 4 == 0) && aligned16(p);
-  v.rscale = rscale;
   return v;
 }
 
@@ -348,7 +347,6 @@ VMat vmat2(const float* p0, int ld0, int rows0, const float* p1, int ld1, int ro
   (void)rows1;
   v.nb = 2;
   v.vec = (ld0 % 4 == 0) && (ld1 % 4 == 0) && aligned16(p0) && aligned16(p1);
-  v.rscale = nullptr;
   return v;
 }
 

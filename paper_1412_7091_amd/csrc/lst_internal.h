@@ -20,13 +20,11 @@ enum {
 };
 
 // ------------------------------------------------------------------ GEMM
-// A "virtual row-major matrix": up to four row blocks stacked on top of each
-// other, each with its own base pointer and leading dimension.  Row r of the
-// virtual matrix lives in block b with r0[b] <= r < r0[b+1].  An optional
-// per-row scale multiplies every element of a row as it is loaded.
+// A "virtual row-major matrix": one or two row blocks stacked on top of each
+// other, each with its own base pointer and leading dimension.  Rows from r1 on
+// live in block 1.
 struct VMat {
   const float* p[2];
-  const float* rscale;  // per-row scale or nullptr
   int ld[2];
   int r1;               // first row of block 1 (nb == 2)
   int nb;
@@ -117,7 +115,7 @@ struct GemmBatch {
 // One-time kernel attribute setup (dynamic LDS limits); call before any launch.
 hipError_t configure_kernels();
 
-VMat vmat(const float* p, int ld, int rows, const float* rscale = nullptr);
+VMat vmat(const float* p, int ld, int rows);
 VMat vmat2(const float* p0, int ld0, int rows0, const float* p1, int ld1, int rows1);
 GemmProblem gemm_problem(int layout, int M, int N, int K, const VMat& A, const VMat& B, float* C,
                          int ldc, float alpha, float beta, int epi);
