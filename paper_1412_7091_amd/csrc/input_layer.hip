@@ -23,12 +23,12 @@
 //   hot     rows of kInputHotSlots slots or more: a block per kPartSlots slots of
 //           the row, 64 to a wave; the sums of rows of several parts are added
 //           in part order by one more launch.
-// Measured at d = 512, m K = 65 536, Zipf 1.1 (the four launches): 15 + 23 + 13
+// Measured at d = 512, m K = 65 536, Zipf 1.1 (the four launches): 19 + 30 + 13
 // + 5 us; uniform rows, update and forward pass together, 126 us (670 before).
 // The table of slots that this replaces took one atomic per slot, 8600 of them
 // at the most frequent row (178 us), and the owner of a repeated row read the
 // later indices to find its slots (398 us), hot rows another 126 us.  m K =
-// 1280, d = 500: 6.3 us (four launches, 21 us).
+// 1280, d = 500: 6.8 us (four launches, 21 us).
 #include <math.h>
 #include <stdlib.h>
 
@@ -74,9 +74,9 @@ constexpr int kInputHashBits = 17;
 constexpr int kInputHashSize = 1 << kInputHashBits;
 static_assert(kInputHashSize >= 2 * kInputMaxSlots, "the row table must stay half empty");
 // Slots up to which the update is one launch: each wave then reads 8 KB of
-// indices, and a row that every slot names (the worst case) takes 55 us, as much
-// as the grouped form; at 2000 slots of a Zipf 1.1 input the one launch takes
-// 14 us, the grouped form 35.
+// indices.  2048 slots at d = 512, update and forward pass together: 18 us for a
+// Zipf 1.1 input (43 grouped), 65 when every slot names one row (35 grouped; 90
+// with the table of slots); 1280 slots at d = 500: 13 (27 grouped).
 constexpr int kInputSmall = 2048;
 constexpr int kSortBlock = 1024;       // slots sorted by one block
 static_assert(kInputMaxSlots / kSortBlock <= 64, "a lane of a wave per sorted block");
