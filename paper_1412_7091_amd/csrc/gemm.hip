@@ -109,7 +109,8 @@ __device__ __forceinline__ floatx4 big_frag(const float* S, int r, int kk) {
 
 template <int TM, int TN, int W, int A_KC, int B_KC>
 __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int total,
-                                                          const int* skip_if, const int* run_if) {
+                                                          const int* skip_if, const int* run_if,
+                                                          int pad) {
   if (skip_if && *skip_if) return;
   if (run_if && !*run_if) return;
   constexpr int WM = TM == 32 ? 1 : 2, WN = 4 / WM;           // waves
@@ -157,7 +158,8 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int tot
   const bool keep = P.epi == EPI_STORE && P.beta != 0.f;
   float* C = P.epi == EPI_PARTIAL ? P.C + (size_t)z * P.M * P.N : P.C;
   const int ldc = P.epi == EPI_PARTIAL ? P.N : P.ldc;
-  const bool vecc = P.N % 4 == 0 && ldc % 4 == 0 && ((uintptr_t)C & 15) == 0;
+  // (with PAD_C a last piece carries zeros past column N: B's rows there are zero)
+  const bool vecc = (P.N % 4 == 0 || (pad & PAD_C)) && ldc % 4 == 0 && ((uintptr_t)C & 15) == 0;
   // Multiplies slice c; with next, slice c + 1 is requested a part at a time
   // between the MFMAs (all of it at once holds the wave for as long as the
   // memory pipeline takes to accept it).
@@ -247,10 +249,11 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int tot
 namespace {
 
 template <int TM, int TN, int W>
-void big_dispatch(const GemmProblem& p, int total, const int* skip_if, const int* run_if,
+void big_dispatch(const GemmProblem& p, int total, const int* skip_if, const int* run_if, int pad,
                   hipStream_t s) {
   auto run = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(total), dim3(256), 0, s, p, total, skip_if, run_if);
+    hipLaunchKernelGGL(kernel, dim3(total), dim3(256), 0, s, p, total, skip_if, run_if,
+                       pad);
   };
   if (p.a_kc && p.b_kc) run(gemm_big_kernel<TM, TN, W, 1, 1>);
   else if (p.a_kc) run(gemm_big_kernel<TM, TN, W, 1, 0>);
@@ -259,9 +262,12 @@ void big_dispatch(const GemmProblem& p, int total, const int* skip_if, const int
 
 }  // namespace
 
-hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if, const int* run_if) {
+hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if, const int* run_if,
+                           int pad) {
   if (p.epi != EPI_STORE && p.epi != EPI_PARTIAL) return hipErrorInvalidValue;
   if (!p.a_kc && p.b_kc) return hipErrorInvalidValue;
+  if ((pad & PAD_K) && (!p.a_kc || p.b_kc)) return hipErrorInvalidValue;
+  if ((pad & PAD_C) && (p.epi != EPI_STORE || p.beta != 0.f || !p.b_kc)) return hipErrorInvalidValue;
   if (p.ksplit < 1) p.ksplit = 1;
   constexpr int kTN = 128;
   // the tile's rows: at most half of them padding (M is the minibatch or D or d)
@@ -270,16 +276,18 @@ hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if, con
   p.tiles_n = (p.N + kTN - 1) / kTN;
   const int total = p.tiles_m * p.tiles_n * (p.epi == EPI_PARTIAL ? p.ksplit : 1);
   if (total == 0) return hipSuccess;
-  // 16-byte LDS-DMA: aligned rows, and whole pieces of a contiguous k
-  const bool v16 = p.A.vec && p.B.vec && ((!p.a_kc && !p.b_kc) || p.K % 4 == 0);
+  // 16-byte LDS-DMA: aligned rows, and whole pieces of a contiguous k (PAD_K: the
+  // last piece's zeros meet the zeros of B's rows past K)
+  const bool v16 = p.A.vec && p.B.vec &&
+                   ((!p.a_kc && !p.b_kc) || p.K % 4 == 0 || (pad & PAD_K));
   if (v16) {
-    if (tmr == 32) big_dispatch<32, kTN, 4>(p, total, skip_if, run_if, s);
-    else if (tmr == 64) big_dispatch<64, kTN, 4>(p, total, skip_if, run_if, s);
-    else big_dispatch<128, kTN, 4>(p, total, skip_if, run_if, s);
+    if (tmr == 32) big_dispatch<32, kTN, 4>(p, total, skip_if, run_if, pad, s);
+    else if (tmr == 64) big_dispatch<64, kTN, 4>(p, total, skip_if, run_if, pad, s);
+    else big_dispatch<128, kTN, 4>(p, total, skip_if, run_if, pad, s);
   } else {
-    if (tmr == 32) big_dispatch<32, kTN, 1>(p, total, skip_if, run_if, s);
-    else if (tmr == 64) big_dispatch<64, kTN, 1>(p, total, skip_if, run_if, s);
-    else big_dispatch<128, kTN, 1>(p, total, skip_if, run_if, s);
+    if (tmr == 32) big_dispatch<32, kTN, 1>(p, total, skip_if, run_if, pad, s);
+    else if (tmr == 64) big_dispatch<64, kTN, 1>(p, total, skip_if, run_if, pad, s);
+    else big_dispatch<128, kTN, 1>(p, total, skip_if, run_if, pad, s);
   }
   return hipGetLastError();
 }

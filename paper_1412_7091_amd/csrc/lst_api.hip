@@ -72,7 +72,8 @@ struct lst_state {
   int n_c1p = 0;  // partial sums of h^T Q h per example (two per 32-column tile of H^)
   int n_hap_max = 0;  // partial sums of |H^T H| per row for m = m_max
   // naive workspace
-  float* O = nullptr;
+  float* O = nullptr;      // m_max x ldo, zeros past column D
+  int64_t ldo = 0;
   float* wsplit = nullptr;
   double* nws = nullptr;  // row sums in chunks
   int naive_ksplit = 1;
@@ -1105,10 +1106,17 @@ int lst_naive_init(lst_state** out, int64_t D, int32_t d, const float* W, const 
   if (ks > 256) ks = 256;
   if (ks < 1) ks = 1;
   s->naive_ksplit = (int)ks;
-  if ((rc = dalloc(s, &s->O, (size_t)m * D)) ||
+  // rows of O are whole 16-byte pieces (D = 100 001, d = 500, m = 128: 594 us a step
+  // with D floats a row, whose products go in 4-byte pieces, and 468 so)
+  s->ldo = D <= 0x7fffffff - 3 ? (D + 3) / 4 * 4 : D;
+  if ((rc = dalloc(s, &s->O, (size_t)m * s->ldo)) ||
       (rc = dalloc(s, &s->wsplit, (size_t)ks * m * d)) ||
       (rc = dalloc(s, &s->nws, naive_ws_doubles(m))))
     return fail(rc);
+  if (s->ldo > D &&
+      hipMemset2DAsync(s->O + D, (size_t)s->ldo * sizeof(float), 0,
+                       (size_t)(s->ldo - D) * sizeof(float), (size_t)m, s->stream) != hipSuccess)
+    return fail(LST_EHIP);
   if (hipMemcpyAsync(s->V, W, (size_t)D * d * sizeof(float), hipMemcpyDeviceToDevice, s->stream) !=
       hipSuccess)
     return fail(LST_EHIP);
@@ -1127,22 +1135,23 @@ int lst_naive_step(lst_state* s, int32_t m, int32_t K, const float* H, const int
   const int64_t D = s->D;
   hipStream_t st = s->stream;
   const bool sq = s->cfg.loss == LST_LOSS_SQUARED;
+  const int ldo = (int)s->ldo;
   // O (m x D) = H^T W^T: every output of every example, O(D d) each
   HIPCHK(gemm_big_launch(gemm_problem(L_NT, m, (int)D, d, vmat(H, d, m), vmat(s->V, d, (int)D),
-                                      s->O, (int)D, 1.f, 0.f, EPI_STORE),
-                         st));
-  HIPCHK(naive_rowstats(s->O, D, D, m, Y_idx, Y_val, K, s->cfg.loss, s->cfg.sph_eps, loss,
+                                      s->O, ldo, 1.f, 0.f, EPI_STORE),
+                         st, nullptr, nullptr, ldo > D ? PAD_C : 0));
+  HIPCHK(naive_rowstats(s->O, ldo, D, m, Y_idx, Y_val, K, s->cfg.loss, s->cfg.sph_eps, loss,
                         s->nws, s->flags, st));
   {  // grad_H = (dL/dO) W  (K = D, split over K)
-    GemmProblem p = gemm_problem(L_NN, m, d, (int)D, vmat(s->O, (int)D, m), vmat(s->V, d, (int)D),
+    GemmProblem p = gemm_problem(L_NN, m, d, (int)D, vmat(s->O, ldo, m), vmat(s->V, d, (int)D),
                                  s->wsplit, d, 1.f, 0.f, EPI_PARTIAL);
     p.ksplit = s->naive_ksplit;
-    HIPCHK(gemm_big_launch(p, st));
+    HIPCHK(gemm_big_launch(p, st, nullptr, nullptr, ldo > D ? PAD_K : 0));
     HIPCHK(gemm_splitk_reduce(s->wsplit, s->naive_ksplit, m, d, grad_H, d, sq ? 2.f : 1.f, 0.f, 0,
                               nullptr, st));
   }
   // W -= lr (dL/dO)^T H^T
-  HIPCHK(gemm_big_launch(gemm_problem(L_TN, (int)D, d, m, vmat(s->O, (int)D, m), vmat(H, d, m),
+  HIPCHK(gemm_big_launch(gemm_problem(L_TN, (int)D, d, m, vmat(s->O, ldo, m), vmat(H, d, m),
                                       s->V, d, sq ? -2.f * lr : -lr, 1.f, EPI_STORE),
                          st, s->flags + F_ERR));
   s->steps += 1;

@@ -120,8 +120,12 @@ VMat vmat2(const float* p0, int ld0, int rows0, const float* p1, int ld1, int ro
 GemmProblem gemm_problem(int layout, int M, int N, int K, const VMat& A, const VMat& B, float* C,
                          int ldc, float alpha, float beta, int epi);
 // One large product (EPI_STORE or EPI_PARTIAL) on 128 x 128 double-buffered tiles.
+// pad: PAD_K when the rows of an A with contiguous k hold zeros from K up to the
+// next multiple of four (B's k being its rows), PAD_C when the rows of C (beta =
+// 0) have room for the zeros of columns N up to there.
+enum { PAD_K = 1, PAD_C = 2 };
 hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if = nullptr,
-                           const int* run_if = nullptr);
+                           const int* run_if = nullptr, int pad = 0);
 // Split-K: C = alpha * sum_z ws[z] + beta * C (sym: r <= c mirrored).
 hipError_t gemm_splitk_reduce(const float* ws, int splits, int M, int N, float* C, int ldc,
                               float alpha, float beta, int sym, const int* skip_if,

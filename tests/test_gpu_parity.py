@@ -235,7 +235,8 @@ def test_wide_minibatch_update_tiles(gpu_lib, m, d):
 
 @pytest.mark.parametrize("m,d,D", [(1, 4, 5), (1, 130, 1000), (31, 33, 700), (32, 128, 4096),
                                    (33, 36, 129), (64, 96, 2051), (65, 260, 3000), (127, 127, 999),
-                                   (128, 129, 3001), (130, 500, 1025), (300, 64, 20000)])
+                                   (128, 129, 3001), (130, 500, 1025), (300, 64, 20000),
+                                   (100, 60, 40002)])
 def test_naive_tile_edges(gpu_lib, m, d, D):
     """The explicit-W products at the edges of their tiles (rows 32, 64, 128; columns 128; k
     slices of 32), aligned and not, with repeated targets; the row sums in one chunk and in
