@@ -158,7 +158,8 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int tot
   const bool keep = P.epi == EPI_STORE && P.beta != 0.f;
   float* C = P.epi == EPI_PARTIAL ? P.C + (size_t)z * P.M * P.N : P.C;
   const int ldc = P.epi == EPI_PARTIAL ? P.N : P.ldc;
-  // (with PAD_C a last piece carries zeros past column N: B's rows there are zero)
+  // (with PAD_C a last piece carries zeros past column N, as B's rows there are
+  // zero; NaN in a row of A that is not finite)
   const bool vecc = (P.N % 4 == 0 || (pad & PAD_C)) && ldc % 4 == 0 && ((uintptr_t)C & 15) == 0;
   // Multiplies slice c; with next, slice c + 1 is requested a part at a time
   // between the MFMAs (all of it at once holds the wave for as long as the

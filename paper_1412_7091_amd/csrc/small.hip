@@ -265,6 +265,8 @@ __global__ __launch_bounds__(256) void naive_chunk_kernel(float* __restrict__ O,
   chunk_range(D, nch, c, b, e);
   float* o = O + (size_t)i * ldo;
   const double sh = loss_kind == LST_LOSS_SPHERICAL_SHIFTED ? (double)eps : 0.0;
+  // the row's padding: NaN after the product if its example is not finite
+  if (c == 0 && t < ldo - D) o[D + t] = 0.f;
   if (loss_kind == LST_LOSS_SQUARED) {
     for (int k = t; k < K; k += 256) {
       const int r = idx[(size_t)i * K + k];

@@ -256,6 +256,32 @@ def test_naive_tile_edges(gpu_lib, m, d, D):
     assert rel(W, extra["W_ref"]) < 1e-5
 
 
+@pytest.mark.parametrize("D", [997, 998, 999, 1000])
+def test_naive_infinite_row(gpu_lib, D):
+    """An infinity in one example: its outputs and gradient are infinite, not NaN, also where the
+    rows of the outputs are padded, and the other examples keep their results."""
+    import paper_1412_7091_amd as lst
+
+    d, m, K = 36, 5, 2
+    rng = np.random.default_rng(D)
+    W = torch.from_numpy(rng.uniform(0.1, 1.0, (D, d)).astype(np.float32)).cuda()
+    H = torch.from_numpy(rng.uniform(0.1, 1.0, (m, d)).astype(np.float32)).cuda()
+    idx = torch.from_numpy(rng.permutation(D)[:m * K].reshape(m, K).astype(np.int32)).cuda()
+    val = torch.ones((m, K), device="cuda")
+    results = []
+    for first in (float(H[2, 3]), float("inf")):
+        H[2, 3] = first
+        layer = lst.NaiveOutputLayer(W, m_max=m, K_max=K)
+        loss, grad = layer.step(H, idx, val, 1e-3)
+        code = layer.sync()
+        results.append((code, loss.cpu(), grad.cpu()))
+    (c0, l0, g0), (c1, l1, g1) = results
+    assert c0 == lst.LST_OK and c1 == lst.LST_ENONFINITE
+    assert torch.isposinf(l1[2]) and torch.isposinf(g1[2]).all()
+    others = [0, 1, 3, 4]
+    assert torch.equal(l0[others], l1[others]) and torch.equal(g0[others], g1[others])
+
+
 @pytest.mark.timeout(600)
 def test_c2_paper_100_steps(gpu_lib):
     """D = 200000, d = 500, m = 128, K = 10, lr = 1e-3 at full size (the benchmarked
