@@ -956,11 +956,12 @@ int lst_step_solve(lst_state* s, int32_t m, int32_t K, const float* H, const int
   if (s->kind != 0) return LST_ESTATE;
   if (s->d > kLuMaxD) return LST_EINVAL;
   DeviceGuard dg(s->device);
-  if (!s->lu_F) {
+  {  // (each by itself: an earlier call may have run out of memory half way)
     const int d = s->d;
-    if ((rc = dalloc(s, &s->lu_F, (size_t)d * d)) ||
-        (rc = dalloc(s, &s->lu_dinv, lu_dinv_floats(d))) || (rc = dalloc(s, &s->lu_piv, d)) ||
-        (rc = dalloc(s, &s->lu_act, 2 * (size_t)d)))
+    if ((!s->lu_F && (rc = dalloc(s, &s->lu_F, (size_t)d * d))) ||
+        (!s->lu_dinv && (rc = dalloc(s, &s->lu_dinv, lu_dinv_floats(d)))) ||
+        (!s->lu_piv && (rc = dalloc(s, &s->lu_piv, d))) ||
+        (!s->lu_act && (rc = dalloc(s, &s->lu_act, 2 * (size_t)d))))
       return rc;
   }
   if (s->prof) s->prof_steps += 1;
