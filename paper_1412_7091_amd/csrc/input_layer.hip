@@ -364,10 +364,16 @@ __global__ __launch_bounds__(256) void input_update_small_kernel(
   if (64 * before >= d) return;
   const int col = 64 * before + lane, colc = min(col, d - 1);
   const float old = W[(size_t)r * d + colc];
+  // in the order of the grouped form: 64 slots, then parts of kPartSlots, then the
+  // parts
   float acc = 0.f;
-  for (int t0 = 0; t0 < cnt; t0 += 64) {
-    const int s = list[w][min(t0 + lane, cnt - 1)];
-    acc += sum_list_col(gA, colc, min(64, cnt - t0), val[s], (unsigned)(s / K) * (unsigned)d);
+  for (int p0 = 0; p0 < cnt; p0 += kPartSlots) {
+    float part = 0.f;
+    for (int t0 = p0; t0 < min(cnt, p0 + kPartSlots); t0 += 64) {
+      const int s = list[w][min(t0 + lane, cnt - 1)];
+      part += sum_list_col(gA, colc, min(64, cnt - t0), val[s], (unsigned)(s / K) * (unsigned)d);
+    }
+    acc += part;
   }
   if (col < d) W[(size_t)r * d + col] = old - lr * acc;
 }

@@ -1,6 +1,8 @@
 """GPU parity of the sparse input layer (section 2.2) against oracle.input_layer,
 through the C ABI.  Inputs: the synth generators' (index, value) pairs as the
 K-sparse inputs x and their H as dL/dA."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -193,3 +195,51 @@ def test_input_layer_bad_index_both_forms(gpu_lib, m, K):
     W_ref = input_layer.update(W.astype(np.float64), idx, val, G, 0.1)
     assert rel(layer.get_W().cpu().numpy(), W_ref) < 1e-6
     layer.close()
+
+
+def _documented_update(W, idx, val, G, lr):
+    """lst_input_update's sums in float32 in the order its header states: pairs in (example,
+    pair) order; from 64 pairs a row on, groups of 64, four groups to a part, then the parts."""
+    W = W.copy()
+    ex, k = np.nonzero(idx >= 0)
+    rows = idx[ex, k]
+    for r in np.unique(rows):
+        at = rows == r
+        terms = val[ex[at], k[at]][:, None] * G[ex[at]]
+        add = lambda xs: functools.reduce(np.add, xs, np.zeros(W.shape[1], np.float32))
+        if len(terms) >= 64:
+            groups = [add(terms[o:o + 64]) for o in range(0, len(terms), 64)]
+            terms = [add(groups[o:o + 4]) for o in range(0, len(groups), 4)]
+        W[r] -= np.float32(lr) * add(terms)
+    return W
+
+
+@pytest.mark.parametrize("d", [37, 64, 516])
+@pytest.mark.parametrize("pairs", [(1, 63, 64, 65, 255), (256, 257, 320), (321, 512, 513),
+                                   (1700,)])
+def test_input_layer_order_of_sums(gpu_lib, pairs, d):
+    """A row's pairs are added in the documented order, in the one-launch form (m K = 2048) and,
+    with one more unused slot an example, in the grouped one (2176): both equal the same sums in
+    float32 bit for bit.  Values and rate are powers of two, so that products are exact and a
+    fused multiply-add rounds as the addition does."""
+    import torch
+
+    rng = np.random.default_rng(sum(pairs) + d)
+    m, K = 128, 16
+    idx = np.full(m * K, -1, np.int32)
+    slots = rng.permutation(m * K)[:sum(pairs)]
+    idx[slots] = np.repeat(np.arange(len(pairs)), pairs)
+    idx = idx.reshape(m, K)
+    val = np.exp2(rng.integers(-2, 3, (m, K))).astype(np.float32)
+    G = rng.standard_normal((m, d)).astype(np.float32)
+    W = rng.standard_normal((len(pairs) + 2, d)).astype(np.float32)
+    want = _documented_update(W, idx, val, G, 0.125)
+    for pad in (0, 1):
+        layer = _layer(W)
+        i_t = torch.from_numpy(np.pad(idx, ((0, 0), (0, pad)), constant_values=-1)).cuda()
+        v_t = torch.from_numpy(np.pad(val, ((0, 0), (0, pad)))).cuda()
+        layer.update(i_t, v_t, torch.from_numpy(G).cuda(), 0.125)
+        assert layer.sync() == 0
+        got = layer.get_W().cpu().numpy()
+        assert np.array_equal(got, want), (pad, np.abs(got - want).max(axis=1))
+        layer.close()
