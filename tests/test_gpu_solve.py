@@ -182,3 +182,65 @@ def test_step_solve_row_solutions(gpu_lib, d, m):
     print(f"d={d} m={m}: {err:.2e} (bound {bound:.2e})", flush=True)
     assert err <= bound
     layer.close()
+
+
+# columns in the first and last of the four waves' shares of a panel (8 columns each), past the
+# first panel and at the end; d = 600 and 1024 start with panels of more than 512 rows
+@pytest.mark.parametrize("d,col", [(8, 0), (8, 7), (100, 3), (100, 12), (100, 31), (100, 32),
+                                   (100, 99), (300, 17), (300, 250), (600, 5), (600, 29),
+                                   (600, 90), (600, 200), (600, 599), (1024, 0), (1024, 31),
+                                   (1024, 500), (1024, 1023)])
+@pytest.mark.parametrize("pivot", ["zero", "infinite"])
+def test_step_solve_singular_columns(gpu_lib, d, col, pivot):
+    """A pivot that vanishes, or is not finite, in column `col` of A = U_new^T only: U is a
+    permutation and h lies along one unit vector, so U_new = U but for one entry, 1 - 8 lr
+    (h = 2 e_j): 0 at lr = 1/8, minus infinity at lr = 3e38.  Nothing is updated."""
+    import paper_1412_7091_amd as lst
+
+    rng = np.random.default_rng(d + col)
+    perm = rng.permutation(d)
+    U = np.zeros((d, d), np.float32)
+    U[np.arange(d), perm] = 1.0
+    H = np.zeros((1, d), np.float32)
+    H[0, perm[col]] = 2.0
+    dev = torch.device("cuda:0")
+    V0 = torch.from_numpy((rng.standard_normal((40, d)) / np.sqrt(d)).astype(np.float32)).to(dev)
+    layer = lst.FactoredOutputLayer(V0, torch.from_numpy(U).to(dev), m_max=1, K_max=1)
+    before = [x.clone() for x in layer.get_state()[:2]] + [layer.get_V().clone()]
+    idx = torch.tensor([[3]], dtype=torch.int32, device=dev)
+    val = torch.tensor([[1.0]], dtype=torch.float32, device=dev)
+    layer.step_solve(torch.from_numpy(H).to(dev), idx, val, 0.125 if pivot == "zero" else 3e38)
+    assert layer.sync() == lst.LST_ESINGULAR
+    after = [x.clone() for x in layer.get_state()[:2]] + [layer.get_V().clone()]
+    for x, y in zip(before, after):
+        assert torch.equal(x, y)
+    # and the next step of the same state is right
+    lr = 0.0625
+    layer.step_solve(torch.from_numpy(H).to(dev), idx, val, lr)
+    assert layer.sync() == 0
+    U_new = U.astype(np.float64)
+    U_new[col, perm[col]] = 1.0 - 8.0 * lr
+    assert rel(layer.get_state()[1].cpu().numpy(), U_new) < 1e-6
+    layer.close()
+
+
+@pytest.mark.parametrize("d", [100, 600])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_step_solve_nonfinite_example(gpu_lib, d, bad):
+    """An example that is not finite: reported by its loss, the factorisation of a U_new full of
+    NaN ends, and nothing is updated."""
+    import paper_1412_7091_amd as lst
+
+    cfg = _cfg(D=300, d=d, m=5, K=2, entropy=430 + d)
+    wl = Workload(cfg)
+    dev = torch.device("cuda:0")
+    layer = lst.FactoredOutputLayer(torch.from_numpy(wl.init_V()).to(dev), m_max=5, K_max=2)
+    before = [x.clone() for x in layer.get_state()[:2]] + [layer.get_V().clone()]
+    H, idx, val = (torch.from_numpy(x).to(dev) for x in wl.batch(0))
+    H[2, d // 2] = bad
+    layer.step_solve(H, idx, val, cfg.lr)
+    assert layer.sync() == lst.LST_ENONFINITE
+    after = [x.clone() for x in layer.get_state()[:2]] + [layer.get_V().clone()]
+    for x, y in zip(before, after):
+        assert torch.equal(x, y)
+    layer.close()
