@@ -125,10 +125,13 @@ def test_input_layer_bad_index_leaves_W(gpu_lib):
 ])
 def test_input_layer_forms_and_edges(gpu_lib, kw):
     """The update's forms at their edges (256, 2048 slots; 64 slots a row; 1024 slots a
-    sorted block), with pads and repeats; the forward pass at K = 16 and beyond.  A row's sum
-    of n products is off by at most n eps times the sum of their magnitudes, which for terms
-    of random sign is sqrt(n) times the result: 2^-24 sqrt(n) n^(1/2) over partial sums of
-    32 and 16 parts stays below 1e-5 up to n = 65 536."""
+    sorted block), with pads and repeats; the forward pass at K = 16 and beyond.  With u =
+    2^-24, an element is off by at most u times its longest chain of roundings times the sum of
+    its terms' magnitudes: the product and up to 64 additions in a group, 4 groups in a part,
+    n / 256 parts, and the subtraction from W (forward: K additions, or a quarter of them and
+    3).  For terms of random sign the roundings of a chain of k add up as sqrt(k) times u times
+    the partial sums, which are about as large as the result: 1.1e-6 of it at n = 65 536
+    (k = 326), for which the norm of the change has 1e-5."""
     cfg = WorkloadConfig(name="inpf", distinct=False, val_dist="normal", pad_frac=0.15,
                          dup_frac=0.2, entropy=4500 + kw["m"] + 7 * kw["K"] + kw["d"],
                          **{"idx_dist": "uniform", **kw})
@@ -137,29 +140,39 @@ def test_input_layer_forms_and_edges(gpu_lib, kw):
     wl = Workload(cfg)
     W = wl.init_V()
     layer = _layer(W)
-    W_ref = W.astype(np.float64)
+    lr = float(np.float32(0.01))
     for s in range(2):
         G, idx, val = wl.batch(s)
         i_t, v_t = torch.from_numpy(idx).cuda(), torch.from_numpy(val).cuda()
         A = layer.forward(i_t, v_t).cpu().numpy().astype(np.float64)
         W_prev = layer.get_W().cpu().numpy()
-        layer.update(i_t, v_t, torch.from_numpy(G).cuda(), 0.01)
+        layer.update(i_t, v_t, torch.from_numpy(G).cuda(), lr)
         assert layer.sync() == 0
         W_new = layer.get_W().cpu().numpy()
         A_ref, dW = np.zeros((cfg.m, cfg.d)), np.zeros((cfg.D, cfg.d))
+        A_abs, dW_abs = A_ref.copy(), dW.copy()
         rows, cols = np.nonzero(idx >= 0)
         at = idx[rows, cols]
         v64 = val[rows, cols].astype(np.float64)
         np.add.at(A_ref, rows, v64[:, None] * W_prev[at].astype(np.float64))
+        np.add.at(A_abs, rows, np.abs(v64[:, None] * W_prev[at]))
         np.add.at(dW, at, v64[:, None] * G[rows].astype(np.float64))
+        np.add.at(dW_abs, at, np.abs(v64[:, None] * G[rows]))
         assert rel(A, A_ref) < 1e-6 + 2.0 ** -24 * np.sqrt(cfg.K), rel(A, A_ref)
-        W_ref = W_prev.astype(np.float64) - 0.01 * dW
+        chain = cfg.K if cfg.K <= 16 else -(-cfg.K // 4) + 3
+        assert np.all(np.abs(A - A_ref) <= 2.0 ** -24 * (chain + 1) * A_abs)
+        W_ref = W_prev.astype(np.float64) - lr * dW
+        n = np.bincount(at, minlength=cfg.D)[:, None]
+        chain = np.minimum(n, 64) + np.minimum(-(-n // 64), 4) + -(-n // 256)
+        # (1.01: the second-order terms)
+        bound = 1.01 * 2.0 ** -24 * ((chain + 2) * lr * dW_abs + np.abs(W_ref))
+        assert np.all(np.abs(W_new - W_ref) <= bound)
         touched = np.unique(at)
         rest = np.setdiff1d(np.arange(cfg.D), touched)
         assert np.array_equal(W_new[rest], W_prev[rest])
         e = rel(W_new[touched] - W_prev[touched].astype(np.float64),
                 W_ref[touched] - W_prev[touched].astype(np.float64))
-        scale = np.abs(W_prev[touched]).max() / max(np.abs(0.01 * dW[touched]).max(), 1e-30)
+        scale = np.abs(W_prev[touched]).max() / max(np.abs(lr * dW[touched]).max(), 1e-30)
         print(f"{kw}: dW {e:.1e}", flush=True)
         # the change itself, to the rounding of its sum and of W
         assert e < 1e-5 + 2.0 ** -23 * scale, e
@@ -242,4 +255,33 @@ def test_input_layer_order_of_sums(gpu_lib, pairs, d):
         assert layer.sync() == 0
         got = layer.get_W().cpu().numpy()
         assert np.array_equal(got, want), (pad, np.abs(got - want).max(axis=1))
+        layer.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(m=1024, K=64, d=36, D=50),                            # every row of several parts
+    dict(m=4096, K=16, d=20, D=30000, idx_dist="zipf", zipf_s=1.0),
+    dict(m=61, K=63, d=64, D=5000, idx_dist="zipf", zipf_s=1.1),
+])
+def test_input_layer_grouped_update_repeats(gpu_lib, kw):
+    """The grouped update lists its rows and parts in the order that blocks arrive; the sums do
+    not depend on it: layers of the same W give the same bits, call after call."""
+    import torch
+
+    wl = Workload(WorkloadConfig(name="inpr", distinct=False, val_dist="normal", pad_frac=0.1,
+                                 dup_frac=0.2, entropy=4700 + kw["m"],
+                                 **{"idx_dist": "uniform", **kw}))
+    W = wl.init_V()
+    layers = [_layer(W) for _ in range(3)]
+    for s in range(3):
+        G, idx, val = (torch.from_numpy(x).cuda() for x in wl.batch(s))
+        got = []
+        for layer in layers:
+            layer.update(idx, val, G, 0.01)
+            assert layer.sync() == 0
+            got.append(layer.get_W().cpu().numpy())
+        assert not np.array_equal(got[0], W)
+        assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+        W = got[0]
+    for layer in layers:
         layer.close()
