@@ -237,9 +237,6 @@ __global__ __launch_bounds__(256) void input_forward_split_kernel(
 // ------------------------------------------------------------------- update
 // Rows of dA in flight in a wave that sums a list, two 256-column chunks each.
 constexpr int kListRows = 8;
-// Loads in flight of a wave that sums 64 columns of a hot row (a row of 2048
-// slots: 52 us, with 32 loads 79).
-constexpr int kHotLoads = 64;
 
 // acc += sum over the list's slots t0 .. t0 + cnt - 1 (cnt <= 64; lane l holds
 // slot l's value v and the offset o of its row of dA) of v dA[row], in order,
@@ -267,23 +264,19 @@ __device__ __forceinline__ void sum_list(const float* gA, int d, int cg, int cnt
   }
 }
 
-// The same for one column a lane (col; offset in bounds for every lane), cnt <=
-// 64: groups of kHotLoads are summed by themselves and then added.
+// The sum for one column a lane (col; offset in bounds for every lane), cnt <= 64,
+// all loads in flight together (a row of 2048 slots: 52 us, with 32 at a time 79).
 __device__ __forceinline__ float sum_list_col(const float* gA, int col, int cnt, float v,
                                               unsigned o) {
+  float g[64];
+#pragma unroll
+  for (int u = 0; u < 64; ++u)
+    g[u] = gA[(unsigned)__builtin_amdgcn_readlane((int)o, min(u, cnt - 1)) + (unsigned)col];
   float acc = 0.f;
-  for (int t0 = 0; t0 < cnt; t0 += kHotLoads) {
-    float g[kHotLoads];
 #pragma unroll
-    for (int u = 0; u < kHotLoads; ++u)
-      g[u] = gA[(unsigned)__builtin_amdgcn_readlane((int)o, min(t0 + u, cnt - 1)) + (unsigned)col];
-    float part = 0.f;
-#pragma unroll
-    for (int u = 0; u < kHotLoads; ++u) {
-      const float vu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), min(t0 + u, 63)));
-      if (t0 + u < cnt) part += vu * g[u];
-    }
-    acc += part;
+  for (int u = 0; u < 64; ++u) {
+    const float vu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), u));
+    if (u < cnt) acc += vu * g[u];
   }
   return acc;
 }
