@@ -378,18 +378,20 @@ int stages_for(const GemmBatch& b, int max_stages = kMaxStages) {
 // Launches 3 and 4 keep at most 4 stages (64 KB): two blocks share a compute
 // unit, so the short tasks run beside the GEMM tiles.
 constexpr int kLaunch34Stages = 4;
-// Above two tiles per compute unit (c5: 1040 tiles in launch 4) two stages
-// (32 KB), so that five tiles share a unit and hide each other's loads:
-// launch 4 at c5 89 -> 75 us; with fewer tiles the deeper ring wins (c2 +0.8 us).
+// Above two tiles per compute unit two stages (32 KB), so that five tiles share
+// a unit and hide each other's loads.  Step at d = 1024, m = 512 (648 tiles in
+// launch 4): 229.0 us, with four stages 235.1; d = 1024, m = 128 (1040): 79.3 and
+// 80.6; d = 768, m = 128 (588): 60.0 and 61.2.  With fewer tiles the deeper ring
+// wins (d = 500, m = 128: +0.8 us).
 constexpr int kManyTiles = 512;
-int launch34_stages(GemmBatch& g) {
+bool many_tiles(const GemmBatch& g) {
   int tiles = 0;
   for (int q = 0; q < g.np; ++q) {
     const int t = g.p[q].tile == 64 ? 64 : 32;
     const int tm = (g.p[q].M + t - 1) / t, tn = (g.p[q].N + t - 1) / t;
     tiles += g.p[q].epi == EPI_SYM ? tm * (tm + 1) / 2 : tm * tn;
   }
-  return tiles > kManyTiles ? 2 : kLaunch34Stages;
+  return tiles > kManyTiles;
 }
 constexpr int kLaunch2Stages64 = 4;
 // Slots a row needs to be scattered by the launch-4 clear blocks instead of its
@@ -655,11 +657,15 @@ int enqueue_step(lst_state* s, hipStream_t st, int32_t m, int32_t K, const float
       L.ntask = 1;
     }
     // 64 x 64 tiles for Q too (half the LDS reads, a quarter of the blocks) when
-    // the tiles of all problems then still are two a compute unit.  d = 1024, m =
-    // 512 (648 tiles): 240 -> 238 us; d = 512, m = 256 (164): 88.6 -> 95, not there.
-    const int t64 = (d + 63) / 64;
-    if (m > 128 && t64 * (t64 + 1) / 2 + (g.np - 1) * t64 * t64 >= kManyTiles) g.p[0].tile = 64;
-    OK_OR_RETURN(run_launch(s, c, L, stages_for(g, launch34_stages(g)), st, PH_LAUNCH4));
+    // the tiles of all problems are still more than two a compute unit.  d = 1024,
+    // m = 512 (648 tiles): 240 -> 238 us; fewer are slower: d = 896, m = 512 (497)
+    // 209 -> 212, d = 768, m = 256 (366) 118 -> 124, d = 512, m = 256 (164) 94 -> 102.
+    if (m > 128) {
+      g.p[0].tile = 64;
+      if (!many_tiles(g)) g.p[0].tile = 32;
+    }
+    OK_OR_RETURN(run_launch(s, c, L, stages_for(g, many_tiles(g) ? 2 : kLaunch34Stages), st,
+                            PH_LAUNCH4));
     if (scratch) {
       StepLaunch C{};
       C.ntask = 1;
