@@ -122,6 +122,8 @@ def test_input_layer_bad_index_leaves_W(gpu_lib):
     dict(m=1024, K=64, d=36, D=50),                            # every row hot, all 64 blocks
     dict(m=4096, K=16, d=20, D=30000, idx_dist="zipf", zipf_s=1.0),
     dict(m=65535, K=1, d=12, D=1),                             # one row, every slot
+    dict(m=9, K=300, d=257, D=500),                            # lists of more than 64 a quarter
+    dict(m=40, K=61, d=6, D=400),
 ])
 def test_input_layer_forms_and_edges(gpu_lib, kw):
     """The update's forms at their edges (256, 2048 slots; 64 slots a row; 1024 slots a
