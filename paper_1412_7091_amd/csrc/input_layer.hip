@@ -11,7 +11,7 @@
 // wave reads all the indices (8 KB at most, in flight together) and so checks
 // them, and finds its row's slots and whether it is the first, without any
 // table.  Larger calls are grouped first (four launches):
-//   group   blocks of 1024 slots sort theirs by (row, slot) in LDS; the first
+//   group   blocks of 256 or 1024 slots sort theirs by (row, slot); the first
 //           slot of each run counts the run in an open-addressing table of the
 //           rows: atomics per block and row, however often the block names it;
 //   update  rows that one block names: the wave of the run sums its slots.  Rows
@@ -23,17 +23,19 @@
 //   hot     rows of kInputHotSlots slots or more: a block per kPartSlots slots of
 //           the row, 64 to a wave; the sums of rows of several parts are added
 //           in part order by one more launch.
-// Measured at d = 512, m K = 65 536, Zipf 1.1 (the four launches): 19 + 30 + 13
-// + 5 us; uniform rows, update and forward pass together, 126 us (670 before).
-// The table of slots that this replaces took one atomic per slot, 8600 of them
-// at the most frequent row (178 us), and the owner of a repeated row read the
-// later indices to find its slots (398 us), hot rows another 126 us.  m K =
-// 1280, d = 500: 6.8 us (four launches, 21 us).
+// Measured at d = 512, m K = 65 536, Zipf 1.1 (the four launches): 15 + 28 + 13
+// + 5 us; uniform rows at d = 500: 95 us.  A table of slots took one atomic per
+// slot, 8600 of them at the most frequent row (178 us), and the owner of a
+// repeated row read the later indices to find its slots (398 us), hot rows
+// another 126 us; uniform rows 870 us, but 18 at 2049 slots, where this form took
+// 24 with blocks of 1024 slots (now 17).  m K = 1280, d = 500: 6.6 us (a table of
+// slots in four launches, 21 us).
 #include <math.h>
 #include <stdlib.h>
 
 #include <algorithm>
 #include <new>
+#include <type_traits>
 
 #include "lst_internal.h"
 
@@ -74,12 +76,18 @@ constexpr int kInputHashBits = 17;
 constexpr int kInputHashSize = 1 << kInputHashBits;
 static_assert(kInputHashSize >= 2 * kInputMaxSlots, "the row table must stay half empty");
 // Slots up to which the update is one launch: each wave then reads 8 KB of
-// indices.  2048 slots at d = 512, update and forward pass together: 18 us for a
-// Zipf 1.1 input (43 grouped), 65 when every slot names one row (35 grouped; 90
-// with the table of slots); 1280 slots at d = 500: 13 (27 grouped).
+// indices.  2048 slots at d = 512: uniform rows 5.7 us (17 grouped), Zipf 1.1 11.8
+// (27), sixteen rows 10.4 (22).  Only where nearly all of more than 768 slots name
+// one row is the grouped form faster (2048 slots: 52 and 22 us), which the host
+// cannot see.
 constexpr int kInputSmall = 2048;
-constexpr int kSortBlock = 1024;       // slots sorted by one block
-static_assert(kInputMaxSlots / kSortBlock <= 64, "a lane of a wave per sorted block");
+// Slots sorted by one block: 256 while that gives at most a block per lane of a
+// wave, else 1024.  The sort is a chain of exchanges, 36 stages for 256 and 55
+// for 1024, whose waves share a compute unit: 2049 slots at d = 500, the whole
+// update, 17 us with blocks of 256 and 24 with 1024; 16 384 slots 31 and 40.
+constexpr int kSortSmall = 256, kSortLarge = 1024;
+constexpr int kSortSmallSlots = 64 * kSortSmall;
+static_assert(kInputMaxSlots / kSortLarge <= 64, "a lane of a wave per sorted block");
 // Rows of this many slots or more are not left to one wave.
 constexpr int kInputHotSlots = 64;
 constexpr int kPartSlots = 256;  // slots of a hot row that one block sums
@@ -388,50 +396,74 @@ __global__ __launch_bounds__(256) void input_update_small_kernel(
   if (col < d) W[(size_t)r * d + col] = old - lr * acc;
 }
 
-// Ascending order of one key per thread over the block (bitonic; strides below
-// 64 by shuffles, the others through LDS).
-__device__ __forceinline__ unsigned long long block_sort_asc(unsigned long long x,
-                                                             unsigned long long* sh) {
-  const int t = threadIdx.x;
-  for (int k = 2; k <= kSortBlock; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      unsigned long long o;
-      if (j >= 64) {
-        sh[t] = x;
-        __syncthreads();
-        o = sh[t ^ j];
-        __syncthreads();
-      } else {
-        o = __shfl_xor(x, j);
-      }
-      const bool up = (t & k) == 0, low = (t & j) == 0;
-      x = (low == up) ? (o < x ? o : x) : (o > x ? o : x);
-    }
+// The value of lane (lane ^ J).
+template <int J>
+__device__ __forceinline__ unsigned lane_xor(unsigned v) {
+  if constexpr (J == 1) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);
+  } else if constexpr (J == 2) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);
+  } else if constexpr (J == 4) {  // 7 - x within eight lanes, then 3 - x within four
+    const int m = __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);
+    return (unsigned)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true);
+  } else if constexpr (J == 8) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true);
+  } else if constexpr (J == 16) {  // [0]: the even rows twice, [1]: the odd ones
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? p[0] : p[1];
+  } else {
+    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32) ? p[0] : p[1];
   }
-  return x;
 }
 
-// Block b sorts slots [1024 b, +1024) by (row, slot) and counts each run in the
+// Ascending order of one key per thread over a block of SB threads (bitonic;
+// strides below 64 between lanes, by DPP and lane swaps, which do not go through
+// the LDS unit as shuffles do; the others through LDS).
+template <int SB, int KK, int J>
+__device__ __forceinline__ void sort_stages(unsigned long long& x, unsigned long long* sh) {
+  const int t = threadIdx.x;
+  unsigned long long o;
+  if constexpr (J >= 64) {
+    sh[t] = x;
+    __syncthreads();
+    o = sh[t ^ J];
+    __syncthreads();
+  } else {
+    o = ((unsigned long long)lane_xor<J>((unsigned)(x >> 32)) << 32) | lane_xor<J>((unsigned)x);
+  }
+  const bool up = (t & KK) == 0, low = (t & J) == 0;
+  x = (low == up) == (o < x) ? o : x;  // (keys are distinct)
+  if constexpr (J > 1)
+    sort_stages<SB, KK, J / 2>(x, sh);
+  else if constexpr (KK < SB)
+    sort_stages<SB, 2 * KK, KK>(x, sh);
+}
+
+// Block b sorts slots [SB b, +SB) by (row, slot) and counts each run in the
 // table; a row is listed as its second run arrives.
-__global__ __launch_bounds__(kSortBlock) void input_group_kernel(
+template <int SB>
+__global__ __launch_bounds__(SB) void input_group_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ val, int n, int K, int d, int64_t D,
     int* srow, uint2* spair, int* rlen, int* rent, int* piv, unsigned long long* table,
     int* multi, int4* part, int* flags) {
-  __shared__ unsigned long long sh[kSortBlock];
-  __shared__ unsigned long long heads[kSortBlock / 64];
-  const int t = threadIdx.x, e = blockIdx.x * kSortBlock + t;
+  __shared__ unsigned long long sh[SB];
+  __shared__ unsigned long long heads[SB / 64];
+  __shared__ float vals[SB];
+  const int t = threadIdx.x, e = blockIdx.x * SB + t;
   if (e == 0) part[0] = make_int4(0, 0, 0, 0);
   const int r = e < n ? idx[e] : -1;
+  vals[t] = e < n ? val[e] : 0.f;
   if (r < -1 || (int64_t)r >= D) atomicCAS(flags, 0, LST_EINDEX);
   const bool valid = r >= 0 && (int64_t)r < D;
   const unsigned row = valid ? (unsigned)r : 0xffffffffu;  // the others last
-  const unsigned long long x =
-      block_sort_asc(((unsigned long long)row << 32) | (unsigned)e, sh);
+  unsigned long long x = ((unsigned long long)row << 32) | (unsigned)e;
+  sort_stages<SB, 2, 1>(x, sh);
   sh[t] = x;
   __syncthreads();
   const unsigned my = (unsigned)(x >> 32);
   const int slot = (int)(unsigned)x;
-  const float v = slot < n ? val[slot] : 0.f;
+  const float v = vals[slot & (SB - 1)];
   const bool head = my != 0xffffffffu && (t == 0 || (unsigned)(sh[t - 1] >> 32) != my);
   const bool end = my == 0xffffffffu;  // no run: ends the one before
   const unsigned long long stop = __ballot(head || end);
@@ -440,9 +472,9 @@ __global__ __launch_bounds__(kSortBlock) void input_group_kernel(
   int len = 0, ent = -1;
   if (head) {
     // up to the next head (or the end of the valid slots)
-    int nx = kSortBlock;
+    int nx = SB;
     unsigned long long m = heads[t >> 6] & (~0ull << (t & 63)) & ~(1ull << (t & 63));
-    for (int q = t >> 6; q < kSortBlock / 64; ++q) {
+    for (int q = t >> 6; q < SB / 64; ++q) {
       if (q > (t >> 6)) m = heads[q];
       if (m != 0ull) {
         nx = 64 * q + __ffsll((unsigned long long)m) - 1;
@@ -451,7 +483,7 @@ __global__ __launch_bounds__(kSortBlock) void input_group_kernel(
     }
     len = nx - t;
   }
-  // the position's arrays are whole blocks (kInputMaxSlots is a multiple of 1024)
+  // the position's arrays are whole blocks (kInputMaxSlots is a multiple of SB)
   const int row_out = end ? 0x7fffffff : (int)my;
   srow[e] = row_out;
   spair[e] = make_uint2((unsigned)(slot / K) * (unsigned)d, __float_as_uint(v));
@@ -477,16 +509,16 @@ __global__ __launch_bounds__(kSortBlock) void input_group_kernel(
 }
 
 // Block b's run of row r: its first position in q, its length returned (0:
-// none).  Four dependent loads: the block's sixteen groups of 64 by their last
-// rows, the group's four of 16, the sixteen rows, the length.
+// none).  Four dependent loads: the block's groups of 64 by their last rows, the group's four of 16, the sixteen rows, the length.
 __device__ __forceinline__ int below(const int4& x, int r) {
   return (x.x < r) + (x.y < r) + (x.z < r) + (x.w < r);
 }
+template <int SB>
 __device__ __forceinline__ int find_run(const int* srow, const int* rlen, const int* piv, int b,
                                         int nb, int r, int& q) {
   q = 0;
   if (b >= nb) return 0;
-  constexpr int kGroups = kSortBlock / 64;
+  constexpr int kGroups = SB / 64;
   const int4* p64 = reinterpret_cast<const int4*>(piv + b * kGroups);
   int grp = 0;
 #pragma unroll
@@ -526,7 +558,8 @@ __device__ __forceinline__ int wave_prefix(int v, int& total) {
 // 4: at the largest Zipf 1.1 call 81 us for update and forward pass, 92 at 16
 // (too few waves for the rows of one slot); with uniform rows 126, 155 at 1.
 constexpr int kRunsPerWave = 4;
-// Blocks (of four waves) for the rows that several blocks name.
+// Blocks (of four waves) for the rows that several blocks name, at most (and no
+// more than a wave per such row).
 constexpr int kMultiBlocks = 1024;
 static_assert(kInputMaxSlots / 2 <= 4 * kMultiBlocks * 64, "a lane for each of a wave's rows");
 
@@ -630,23 +663,24 @@ __device__ __forceinline__ void update_runs(float* W, const float* gA, int d, fl
   }
 }
 
-template <bool VEC>
+template <int SB, bool VEC>
 __global__ __launch_bounds__(256) void input_update_kernel(
     float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
     const uint2* spair, const int* rlen, const int* rent, const int* piv,
-    unsigned long long* table, const int* multi, int4* part, int4* split, const int* flags) {
+    unsigned long long* table, const int* multi, int4* part, int4* split, const int* flags,
+    int multi_blocks) {
   __shared__ uint2 list[4][kInputHotSlots];
   const int w = wave_index(), lane = threadIdx.x & 63;
-  const int nb = (n + kSortBlock - 1) / kSortBlock;
+  const int nb = (n + SB - 1) / SB;
   const int pending = *flags;
-  if (blockIdx.x >= kMultiBlocks) {
-    const int p0 = (((int)blockIdx.x - kMultiBlocks) * 4 + w) * kRunsPerWave;
-    if (p0 >= nb * kSortBlock) return;
+  if ((int)blockIdx.x >= multi_blocks) {
+    const int p0 = (((int)blockIdx.x - multi_blocks) * 4 + w) * kRunsPerWave;
+    if (p0 >= nb * SB) return;
     update_runs<VEC>(W, gA, d, lr, p0, srow, spair, rlen, rent, table, part, split, pending);
     return;
   }
   // The listed rows wv, wv + nw, ...: one a lane, then one after another.
-  const int wv = (int)blockIdx.x * 4 + w, nw = 4 * kMultiBlocks;
+  const int wv = (int)blockIdx.x * 4 + w, nw = 4 * multi_blocks;
   const int count = multi[0];
   const int at = wv + nw * lane;
   int row = -1;
@@ -659,7 +693,7 @@ __global__ __launch_bounds__(256) void input_update_kernel(
   for (int l = 0; wv + nw * l < count; ++l) {
     const int r = __builtin_amdgcn_readlane(row, l);
     int q, total;
-    const int mine = find_run(srow, rlen, piv, lane, nb, r, q);
+    const int mine = find_run<SB>(srow, rlen, piv, lane, nb, r, q);
     const int off = wave_prefix(mine, total);
     if (total >= kInputHotSlots) {
       list_parts(r, total, part, split);
@@ -680,14 +714,14 @@ constexpr int kHotBlocks = 1024;
 
 // One part: kPartSlots slots of a hot row, in order, 64 to each wave; the four
 // sums are added in wave order.  The row itself is updated if this is all of it.
-template <bool VEC>
+template <int SB, bool VEC>
 __global__ __launch_bounds__(256) void input_hot_kernel(
     float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
     const uint2* spair, const int* rlen, const int* piv, int* multi, const int4* part, float* psum,
     const int* flags) {
   __shared__ float4 sums[3][2][64];
   __shared__ int s_off[64], s_q[64];
-  const int nb = (n + kSortBlock - 1) / kSortBlock;
+  const int nb = (n + SB - 1) / SB;
   const int w = wave_index(), lane = threadIdx.x & 63;
   if (blockIdx.x == 0 && threadIdx.x == 0) multi[0] = 0;  // its rows are done
   const int count = *flags != 0 ? 0 : part[0].x;
@@ -698,7 +732,7 @@ __global__ __launch_bounds__(256) void input_hot_kernel(
               sum0 = __builtin_amdgcn_readfirstlane(pt.w);
     if (w == 0) {
       int q, all;
-      const int mine = find_run(srow, rlen, piv, lane, nb, r, q);
+      const int mine = find_run<SB>(srow, rlen, piv, lane, nb, r, q);
       s_off[lane] = wave_prefix(mine, all);
       s_q[lane] = q;
     }
@@ -891,24 +925,29 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
           : run(input_update_small_kernel<kInputSmall / 64, false>);
     return hipGetLastError() == hipSuccess ? LST_OK : LST_EHIP;
   }
-  const int nb = (n + kSortBlock - 1) / kSortBlock;
-  hipLaunchKernelGGL(input_group_kernel, dim3(nb), dim3(kSortBlock), 0, s->stream, idx, val, n, K,
-                     s->d, s->D, s->srow, s->spair, s->rlen, s->rent, s->piv, s->table, s->multi,
-                     s->part, s->flags);
-  const dim3 grid((unsigned)(kMultiBlocks + nb * kSortBlock / (4 * kRunsPerWave)));
-  auto update = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s->stream, s->W, s->d, grad_A, n, lr, s->srow,
-                       s->spair, s->rlen, s->rent, s->piv, s->table, s->multi, s->part, s->split,
-                       s->flags);
-  };
-  vec ? update(input_update_kernel<true>) : update(input_update_kernel<false>);
   const int parts = n / kInputHotSlots + n / kPartSlots;  // at most
-  auto hot = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(parts, kHotBlocks)), dim3(256), 0,
-                       s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair, s->rlen, s->piv,
-                       s->multi, s->part, s->psum, s->flags);
+  auto grouped = [&](auto block, auto vec16) {
+    constexpr int SB = decltype(block)::value;
+    constexpr bool VEC = decltype(vec16)::value;
+    const int nb = (n + SB - 1) / SB;
+    hipLaunchKernelGGL(input_group_kernel<SB>, dim3(nb), dim3(SB), 0, s->stream, idx, val, n, K,
+                       s->d, s->D, s->srow, s->spair, s->rlen, s->rent, s->piv, s->table, s->multi,
+                       s->part, s->flags);
+    const int multi_blocks = std::min(kMultiBlocks, (n / 2 + 3) / 4);
+    hipLaunchKernelGGL((input_update_kernel<SB, VEC>),
+                       dim3((unsigned)(multi_blocks + nb * SB / (4 * kRunsPerWave))), dim3(256), 0,
+                       s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair, s->rlen, s->rent,
+                       s->piv, s->table, s->multi, s->part, s->split, s->flags, multi_blocks);
+    hipLaunchKernelGGL((input_hot_kernel<SB, VEC>), dim3((unsigned)std::min(parts, kHotBlocks)),
+                       dim3(256), 0, s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair,
+                       s->rlen, s->piv, s->multi, s->part, s->psum, s->flags);
   };
-  vec ? hot(input_hot_kernel<true>) : hot(input_hot_kernel<false>);
+  constexpr std::integral_constant<int, kSortSmall> small_block{};
+  constexpr std::integral_constant<int, kSortLarge> large_block{};
+  if (n <= kSortSmallSlots)
+    vec ? grouped(small_block, std::true_type{}) : grouped(small_block, std::false_type{});
+  else
+    vec ? grouped(large_block, std::true_type{}) : grouped(large_block, std::false_type{});
   const int most = (n / kPartSlots) * ((s->d + 63) / 64);
   hipLaunchKernelGGL(input_split_kernel, dim3((unsigned)std::min((most + 3) / 4, kHotBlocks)),
                      dim3(256), 0, s->stream, s->W, s->d, lr, s->part, s->split, s->psum,

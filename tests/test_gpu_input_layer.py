@@ -122,12 +122,15 @@ def test_input_layer_bad_index_leaves_W(gpu_lib):
     dict(m=1024, K=64, d=36, D=50),                            # every row hot, all 64 blocks
     dict(m=4096, K=16, d=20, D=30000, idx_dist="zipf", zipf_s=1.0),
     dict(m=65535, K=1, d=12, D=1),                             # one row, every slot
+    dict(m=16384, K=1, d=33, D=3000),                          # 64 sorted blocks of 256
+    dict(m=1024, K=16, d=3, D=50),                             # and every row hot in all of them
+    dict(m=16385, K=1, d=66, D=20000),                         # blocks of 1024
     dict(m=9, K=300, d=257, D=500),                            # lists of more than 64 a quarter
     dict(m=40, K=61, d=6, D=400),
 ])
 def test_input_layer_forms_and_edges(gpu_lib, kw):
-    """The update's forms at their edges (256, 2048 slots; 64 slots a row; 1024 slots a
-    sorted block), with pads and repeats; the forward pass at K = 16 and beyond.  With u =
+    """The update's forms at their edges (256, 2048, 16 384 slots; 64 slots a row; 256 and 1024
+    slots a sorted block), with pads and repeats; the forward pass at K = 16 and beyond.  With u =
     2^-24, an element is off by at most u times its longest chain of roundings times the sum of
     its terms' magnitudes: the product and up to 64 additions in a group, 4 groups in a part,
     n / 256 parts, and the subtraction from W (forward: K additions, or a quarter of them and
