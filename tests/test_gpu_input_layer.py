@@ -290,3 +290,29 @@ def test_input_layer_grouped_update_repeats(gpu_lib, kw):
         W = got[0]
     for layer in layers:
         layer.close()
+
+
+@pytest.mark.parametrize("m,K,d", [(3, 5, 4), (100, 12, 260), (130, 20, 512), (700, 4, 36)])
+def test_input_layer_unaligned_buffers(gpu_lib, m, K, d):
+    """Activations and gradients that start at a 4-byte address take the same sums in the same
+    order as aligned ones: equal bits."""
+    import torch
+
+    rng = np.random.default_rng(m + K + d)
+    W = rng.standard_normal((90, d)).astype(np.float32)
+    idx = torch.from_numpy(rng.integers(-1, 90, (m, K)).astype(np.int32)).cuda()
+    val = torch.from_numpy(rng.standard_normal((m, K)).astype(np.float32)).cuda()
+    G = torch.from_numpy(rng.standard_normal((m, d)).astype(np.float32)).cuda()
+    results = []
+    for off in (0, 1):
+        layer = _layer(W)
+        G_o, A = (torch.empty(m * d + 4, device="cuda")[off:off + m * d].view(m, d)
+                  for _ in range(2))
+        G_o.copy_(G)
+        layer.update(idx, val, G_o, 0.03)
+        layer.forward(idx, val, out=A)
+        assert layer.sync() == 0
+        results.append((layer.get_W().cpu().numpy(), A.cpu().numpy()))
+        layer.close()
+    for a, b in zip(*results):
+        assert np.array_equal(a, b)
