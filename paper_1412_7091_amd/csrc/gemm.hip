@@ -30,63 +30,77 @@ constexpr int GB_BK = 32;
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// Rows [o0, o0 + T) x k in [k0, k0 + 32) of a k-contiguous operand into S as
-// S[row][slot ^ (row & 7)], zeros outside [0, nout) x [0, kend); W floats a
-// lane and DMA instruction (W = 4: aligned rows, kend % 4 == 0).
-template <int T, int W>
-__device__ __forceinline__ void big_fill_kc(const VMat& v, int o0, int nout, int k0, int kend,
-                                            float* S, int part, int parts) {
+// Place of a 16-byte piece of an operand's slice: pieces e = 0 .. 8 T - 1, in the
+// order of S and, up to the swizzle, of memory.  k-contiguous: rows [o0, o0 + T) x
+// k in [k0, k0 + 32) as S[row][slot ^ (row & 7)].  Otherwise k in [k0, k0 + 32) x
+// columns [o0, o0 + T) as S[k][slot ^ (8 if k & 4)] (the two halves of a wave read
+// rows k and k + 4 together).  slot: the memory's slot that piece e of S holds.
+template <int T, int KC>
+struct BigPiece {
+  static constexpr int SLOTS = KC ? GB_BK / 4 : T / 4;
+  static constexpr int SW = T / 4 >= 16 ? 8 : 4;  // T = 32: 8 slots a row
+  int row, slot;
+  __device__ __forceinline__ explicit BigPiece(int e)
+      : row(e / SLOTS), slot((e % SLOTS) ^ (KC ? row & 7 : (row & 4) ? SW : 0)) {}
+};
+
+// A slice by LDS-DMA, zeros outside [0, nout) x [0, kend): rows of both operands
+// 16-byte aligned; k-contiguous: kend % 4 == 0; otherwise the last piece of a row
+// may carry columns >= nout, which reach only outputs that are not stored.
+template <int T, int KC>
+__device__ __forceinline__ void big_fill(const VMat& v, int o0, int nout, int k0, int kend,
+                                         float* S, int part, int parts) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned base = lds_u32(S);
-  constexpr int NI = T * GB_BK / (64 * W) / 4;
+  constexpr int NI = T * GB_BK / 256 / 4;
 #pragma unroll
   for (int u = 0; u < NI; ++u) {
     if (u * parts / NI != part) continue;
-    const int j = wave + 4 * u, e = 64 * j + lane;
-    int row, k;
-    if (W == 4) {
-      row = e >> 3;
-      k = k0 + 4 * ((e & 7) ^ (row & 7));
-    } else {
-      row = e >> 5;
-      k = k0 + 4 * (((e >> 2) & 7) ^ (row & 7)) + (e & 3);
-    }
-    const int o = o0 + row;
-    const float* gp = (o < nout && k < kend) ? vm_row(v, o) + k : g_dma_zero;
-    if (W == 4) dma16(gp, base + 1024u * j);
-    else dma4(gp, base + 256u * j);
+    const int j = wave + 4 * u;
+    const BigPiece<T, KC> p(64 * j + lane);
+    const int o = o0 + (KC ? p.row : 4 * p.slot), k = k0 + (KC ? 4 * p.slot : p.row);
+    const float* gp =
+        o < nout && k < kend ? vm_row(v, KC ? o : k) + (KC ? k : o) : g_dma_zero;
+    dma16(gp, base + 1024u * j);
   }
 }
 
-// k in [k0, k0 + 32) x columns [o0, o0 + T) of an operand whose rows are k into
-// S as S[k][slot ^ (8 if k & 4)] (the two halves of a wave read rows k and k +
-// 4 together), zeros outside; W = 4: aligned rows; the last piece of a row may
-// carry columns >= nout, which reach only outputs that are not stored.
-template <int T, int W>
-__device__ __forceinline__ void big_fill_nk(const VMat& v, int o0, int nout, int k0, int kend,
-                                            float* S, int part, int parts) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const unsigned base = lds_u32(S);
-  constexpr int NI = T * GB_BK / (64 * W) / 4, SLOTS = T / 4;
-  constexpr int SW = SLOTS >= 16 ? 8 : 4;  // T = 32: 8 slots a row
+// A slice through registers, for rows that are not aligned: loads of 16 bytes at
+// 4-byte addresses, element by element where a piece crosses the operand's end.
+// An LDS-DMA lane takes only 4 bytes an instruction there: V U at D = 50 000, d =
+// 126: 47 us against 39 so, d = 301: 192 and 153; a step of the explicit layer at
+// D = 20 000, d = 514, m = 500: 689 and 534.
+typedef float floatx4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int T, int KC>
+struct BigRegs {
+  static constexpr int NI = T * GB_BK / 4 / 256;
+  floatx4 x[NI];
+  __device__ __forceinline__ void load(const VMat& v, int o0, int nout, int k0, int kend) {
 #pragma unroll
-  for (int u = 0; u < NI; ++u) {
-    if (u * parts / NI != part) continue;
-    const int j = wave + 4 * u, e = 64 * j + lane;
-    int kr, o;
-    if (W == 4) {
-      kr = e / SLOTS;
-      o = o0 + 4 * ((e % SLOTS) ^ ((kr & 4) ? SW : 0));
-    } else {
-      kr = e / T;
-      o = o0 + 4 * (((e % T) >> 2) ^ ((kr & 4) ? SW : 0)) + (e & 3);
+    for (int u = 0; u < NI; ++u) {
+      const BigPiece<T, KC> p(threadIdx.x + 256 * u);
+      const int o = o0 + (KC ? p.row : 4 * p.slot), k = k0 + (KC ? 4 * p.slot : p.row);
+      const int left = o < nout && k < kend ? (KC ? kend - k : nout - o) : 0;
+      x[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (left > 0) {
+        const float* gp = vm_row(v, KC ? o : k) + (KC ? k : o);
+        if (left >= 4) {
+          x[u] = *reinterpret_cast<const floatx4_a4*>(gp);
+        } else {
+          x[u][0] = gp[0];
+          if (left > 1) x[u][1] = gp[1];
+          if (left > 2) x[u][2] = gp[2];
+        }
+      }
     }
-    const int k = k0 + kr;
-    const float* gp = (k < kend && o < nout) ? vm_row(v, k) + o : g_dma_zero;
-    if (W == 4) dma16(gp, base + 1024u * j);
-    else dma4(gp, base + 256u * j);
   }
-}
+  __device__ __forceinline__ void store(float* S) const {
+#pragma unroll
+    for (int u = 0; u < NI; ++u)
+      *reinterpret_cast<floatx4*>(S + 4 * (threadIdx.x + 256 * u)) = x[u];
+  }
+};
 
 // The MFMA operand of row r (of T) for the k of an 8-wide slice at kk: register
 // q of half h = lane / 32 holds k = kk + 4 h + q.
@@ -107,7 +121,7 @@ __device__ __forceinline__ floatx4 big_frag(const float* S, int r, int kk) {
   }
 }
 
-template <int TM, int TN, int W, int A_KC, int B_KC>
+template <int TM, int TN, bool DMA, int A_KC, int B_KC>
 __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int total,
                                                           const int* skip_if, const int* run_if,
                                                           int pad) {
@@ -146,10 +160,8 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int tot
   auto fill = [&](int c, int p, int parts) __attribute__((always_inline)) {
     float* S = smem[c & 1];
     const int k0 = kb + c * GB_BK;
-    if (A_KC) big_fill_kc<TM, W>(A, m0, P.M, k0, ke, S, p, parts);
-    else big_fill_nk<TM, W>(A, m0, P.M, k0, ke, S, p, parts);
-    if (B_KC) big_fill_kc<TN, W>(B, n0, P.N, k0, ke, S + AF, p, parts);
-    else big_fill_nk<TN, W>(B, n0, P.N, k0, ke, S + AF, p, parts);
+    big_fill<TM, A_KC>(A, m0, P.M, k0, ke, S, p, parts);
+    big_fill<TN, B_KC>(B, n0, P.N, k0, ke, S + AF, p, parts);
   };
   const int nch = (ke - kb + GB_BK - 1) / GB_BK;
   // output row of block i, first of the four output columns of group q of block j
@@ -191,13 +203,36 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int tot
                                                              acc[i][j], 0, 0, 0);
     }
   };
-  if (nch > 0) fill(0, 0, 1);
-  for (int c = 0; c + 1 < nch; ++c) {
+  if constexpr (DMA) {
+    if (nch > 0) fill(0, 0, 1);
+    for (int c = 0; c + 1 < nch; ++c) {
+      wait_vm_le(0);
+      lds_barrier();  // slice c has landed; every wave is done with slice c - 1
+      multiply(c, true);
+    }
     wait_vm_le(0);
-    lds_barrier();  // slice c has landed; every wave is done with slice c - 1
-    multiply(c, true);
+  } else {
+    BigRegs<TM, A_KC> ra;
+    BigRegs<TN, B_KC> rb;
+    auto load = [&](int c) __attribute__((always_inline)) {
+      ra.load(A, m0, P.M, kb + c * GB_BK, ke);
+      rb.load(B, n0, P.N, kb + c * GB_BK, ke);
+    };
+    auto store = [&](int c) __attribute__((always_inline)) {
+      ra.store(smem[c & 1]);
+      rb.store(smem[c & 1] + AF);
+    };
+    if (nch > 0) {
+      load(0);
+      store(0);
+    }
+    for (int c = 0; c + 1 < nch; ++c) {
+      lds_barrier();  // as above
+      load(c + 1);
+      multiply(c, false);
+      store(c + 1);
+    }
   }
-  wait_vm_le(0);
   lds_barrier();
   floatx4 old[IM][IN][4];
   if (keep) {
@@ -249,16 +284,16 @@ __global__ __launch_bounds__(256, 2) void gemm_big_kernel(GemmProblem P, int tot
 
 namespace {
 
-template <int TM, int TN, int W>
+template <int TM, int TN, bool DMA>
 void big_dispatch(const GemmProblem& p, int total, const int* skip_if, const int* run_if, int pad,
                   hipStream_t s) {
   auto run = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(total), dim3(256), 0, s, p, total, skip_if, run_if,
                        pad);
   };
-  if (p.a_kc && p.b_kc) run(gemm_big_kernel<TM, TN, W, 1, 1>);
-  else if (p.a_kc) run(gemm_big_kernel<TM, TN, W, 1, 0>);
-  else run(gemm_big_kernel<TM, TN, W, 0, 0>);
+  if (p.a_kc && p.b_kc) run(gemm_big_kernel<TM, TN, DMA, 1, 1>);
+  else if (p.a_kc) run(gemm_big_kernel<TM, TN, DMA, 1, 0>);
+  else run(gemm_big_kernel<TM, TN, DMA, 0, 0>);
 }
 
 }  // namespace
@@ -277,18 +312,18 @@ hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if, con
   p.tiles_n = (p.N + kTN - 1) / kTN;
   const int total = p.tiles_m * p.tiles_n * (p.epi == EPI_PARTIAL ? p.ksplit : 1);
   if (total == 0) return hipSuccess;
-  // 16-byte LDS-DMA: aligned rows, and whole pieces of a contiguous k (PAD_K: the
-  // last piece's zeros meet the zeros of B's rows past K)
+  // LDS-DMA takes pieces of 16 bytes: aligned rows, and whole pieces of a contiguous
+  // k (PAD_K: the last piece's zeros meet the zeros of B's rows past K)
   const bool v16 = p.A.vec && p.B.vec &&
                    ((!p.a_kc && !p.b_kc) || p.K % 4 == 0 || (pad & PAD_K));
   if (v16) {
-    if (tmr == 32) big_dispatch<32, kTN, 4>(p, total, skip_if, run_if, pad, s);
-    else if (tmr == 64) big_dispatch<64, kTN, 4>(p, total, skip_if, run_if, pad, s);
-    else big_dispatch<128, kTN, 4>(p, total, skip_if, run_if, pad, s);
+    if (tmr == 32) big_dispatch<32, kTN, true>(p, total, skip_if, run_if, pad, s);
+    else if (tmr == 64) big_dispatch<64, kTN, true>(p, total, skip_if, run_if, pad, s);
+    else big_dispatch<128, kTN, true>(p, total, skip_if, run_if, pad, s);
   } else {
-    if (tmr == 32) big_dispatch<32, kTN, 1>(p, total, skip_if, run_if, pad, s);
-    else if (tmr == 64) big_dispatch<64, kTN, 1>(p, total, skip_if, run_if, pad, s);
-    else big_dispatch<128, kTN, 1>(p, total, skip_if, run_if, pad, s);
+    if (tmr == 32) big_dispatch<32, kTN, false>(p, total, skip_if, run_if, pad, s);
+    else if (tmr == 64) big_dispatch<64, kTN, false>(p, total, skip_if, run_if, pad, s);
+    else big_dispatch<128, kTN, false>(p, total, skip_if, run_if, pad, s);
   }
   return hipGetLastError();
 }

@@ -282,6 +282,31 @@ def test_naive_infinite_row(gpu_lib, D):
     assert torch.equal(l0[others], l1[others]) and torch.equal(g0[others], g1[others])
 
 
+@pytest.mark.parametrize("m,d,D", [(5, 4, 30), (30, 36, 997), (64, 100, 1030), (128, 132, 2001),
+                                   (130, 260, 1500)])
+def test_naive_unaligned_rows(gpu_lib, m, d, D):
+    """Hidden rows that start at a 4-byte address reach the explicit-W products through
+    registers instead of LDS-DMA; the products and sums are the same: equal bits."""
+    import paper_1412_7091_amd as lst
+
+    K = 3
+    rng = np.random.default_rng(m + d + D)
+    W = torch.from_numpy(rng.standard_normal((D, d)).astype(np.float32)).cuda()
+    H0 = torch.from_numpy((rng.standard_normal((m, d)) / np.sqrt(d)).astype(np.float32)).cuda()
+    idx = torch.from_numpy(rng.integers(0, D, (m, K)).astype(np.int32)).cuda()
+    val = torch.from_numpy(rng.standard_normal((m, K)).astype(np.float32)).cuda()
+    results = []
+    for off in (0, 1):
+        H = torch.empty(m * d + 4, device="cuda")[off:off + m * d].view(m, d)
+        H.copy_(H0)
+        layer = lst.NaiveOutputLayer(W, m_max=m, K_max=K)
+        loss, grad = layer.step(H, idx, val, 1e-3)
+        assert layer.sync() == lst.LST_OK
+        results.append((loss.cpu(), grad.cpu(), layer.materialize_W().cpu()))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.timeout(600)
 def test_c2_paper_100_steps(gpu_lib):
     """D = 200000, d = 500, m = 128, K = 10, lr = 1e-3 at full size (the benchmarked
