@@ -7,8 +7,9 @@ namespace lst {
 
 // ---------------------------------------------------------------------------
 // Large products (the naive explicit-W baseline, V U, the initial W^T W): TM x
-// 128 output tiles, K in slices of 32 that LDS-DMA brings into one of two LDS
-// stages while the other is multiplied, four waves of 32 x 32 blocks on
+// 128 output tiles, K in slices of 32 that LDS-DMA (BigRegs for rows that are not
+// aligned) brings into one of two LDS stages while the other is multiplied, four
+// waves of 32 x 32 blocks on
 // v_mfma_f32_32x32x2f32.  Bound by the fp32 MFMA rate from m = 128 on, by
 // memory below about m = 64 (TM follows M, so that padding is not multiplied).
 //   - 64 KB of LDS (TM = 128): two workgroups share a compute unit, and one
@@ -306,7 +307,8 @@ hipError_t gemm_big_launch(GemmProblem p, hipStream_t s, const int* skip_if, con
   if ((pad & PAD_C) && (p.epi != EPI_STORE || p.beta != 0.f || !p.b_kc)) return hipErrorInvalidValue;
   if (p.ksplit < 1) p.ksplit = 1;
   constexpr int kTN = 128;
-  // the tile's rows: at most half of them padding (M is the minibatch or D or d)
+  // the tile's rows: for M >= 16 at most half of them padding (M is the minibatch
+  // or D or d)
   const int tmr = p.M <= 32 ? 32 : p.M <= 64 ? 64 : 128;
   p.tiles_m = (p.M + tmr - 1) / tmr;
   p.tiles_n = (p.N + kTN - 1) / kTN;

@@ -1113,8 +1113,8 @@ int lst_naive_init(lst_state** out, int64_t D, int32_t d, const float* W, const 
   if (ks > 256) ks = 256;
   if (ks < 1) ks = 1;
   s->naive_ksplit = (int)ks;
-  // rows of O are whole 16-byte pieces (D = 100 001, d = 500, m = 128: 594 us a step
-  // with D floats a row, whose products go in 4-byte pieces, and 468 so)
+  // rows of O are whole 16-byte pieces (D = 100 001, d = 500, m = 128: 483 us a step
+  // with D floats a row, whose products go through registers, and 447 so)
   s->ldo = D <= 0x7fffffff - 3 ? (D + 3) / 4 * 4 : D;
   if ((rc = dalloc(s, &s->O, (size_t)m * s->ldo)) ||
       (rc = dalloc(s, &s->wsplit, (size_t)ks * m * d)) ||

@@ -119,7 +119,8 @@ VMat vmat(const float* p, int ld, int rows);
 VMat vmat2(const float* p0, int ld0, int rows0, const float* p1, int ld1, int rows1);
 GemmProblem gemm_problem(int layout, int M, int N, int K, const VMat& A, const VMat& B, float* C,
                          int ldc, float alpha, float beta, int epi);
-// One large product (EPI_STORE or EPI_PARTIAL) on 128 x 128 double-buffered tiles.
+// One large product (EPI_STORE or EPI_PARTIAL) on double-buffered tiles of 32, 64 or
+// 128 rows (by M) and 128 columns.
 // pad: PAD_K when the rows of an A with contiguous k hold zeros from K up to the
 // next multiple of four (B's k being its rows), PAD_C when the rows of C (beta =
 // 0) have room for the zeros of columns N up to there.

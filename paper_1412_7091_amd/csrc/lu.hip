@@ -40,11 +40,15 @@
 // (1.4 ms when a link was three barriers and ten shuffles and the interchanges
 // and the update were launches of their own; 0.5 ms for the solves with a
 // launch per 64 unknowns on m / 16 workgroups).  The 16 panel launches take 34
-// us (500 rows) down to 17, of which the update's loads and substitution are
-// 9 to 4 us and the links the rest: 0.7 us each at 500 rows (7 columns of 8
-// rows per lane to update, in one wave), 0.25 at 32.  With panel_links for all
-// sizes a link was 0.75 us and the step 585 us instead of 553 (d = 256: 304
-// instead of 279; d = 1024, whose first half keeps them: 1506 and 1459).
+// us (468 rows; the first, whose columns are cold, 42) down to 17 (52 rows and
+// the last): the update's loads, substitution and products 8 to 4 us, the links
+// 20 to 11 us, which is 0.63 us each at 468 rows (7 columns of 8 rows per lane to
+// update, in one wave) and 0.33 at 52, the write-back 4 to 1 us, about 1.5 us
+// outside the kernel's body.  The last launch has 20 links (7 us) and the
+// inverses of its own diagonal blocks (6 us), which the others leave to the next
+// launch.  With panel_links for all sizes a link was 0.75 us and the step 585 us
+// instead of 553 (d = 256: 304 instead of 279; d = 1024, whose first half keeps
+// them at 1.1 us a link, write-back included: 1506 and 1459).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -781,7 +785,8 @@ hipError_t lu_factor(float* A, int d, int* piv, int* act, float* dinv, int* flag
     const LuArgs a{A, d, j0, piv, act + (p & 1) * d, act + ((p & 1) ^ 1) * d, dinv, flags};
     // the columns right of the panel, and the previous panel's diagonal blocks
     const int blocks = j0 == 0 ? 1 : 1 + (R > kNB ? (R - kNB + kNB - 1) / kNB : 0) + 1;
-    // one active row per thread; fewer waves make the link's barrier shorter
+    // a thread per active row, in the update's products and the write-back (above
+    // 512 rows also in the links, whose barriers are shorter with fewer waves)
     const hipError_t e = R <= 256   ? panel_launch<256>(a, blocks, vec, s)
                          : R <= 512 ? panel_launch<512>(a, blocks, vec, s)
                                     : panel_launch<1024>(a, blocks, vec, s);
