@@ -660,10 +660,9 @@ enum : unsigned { TILE32 = 1, TILE64 = 2 };
 // with problems of several K the first gives some XCDs only the long tiles.
 // SHARES belongs to the kernels built for m > 128.  D = 500 000, d = 1024, m =
 // 512: step 249 -> 240 us; d = 512, m = 256: 90.2 -> 88.6.  In the kernels for m
-// <= 128, where it costs an index computation in every tile of a shorter launch,
-// it loses at d = 500, m = 128 (40.5 -> 41.0) and d = 1024, m = 16 (53.9 -> 55.6),
-// and would gain at d = 768 (60.0 -> 59.0) and d = 1024, m = 128 (79.3 -> 77.0);
-// they keep one form.  Only the tile edges in TILES, the layouts in VARS and the
+// <= 128 it loses at d = 500, m = 128 (40.5 -> 41.0) and d = 1024, m = 16 (53.9 ->
+// 55.6) and gains at m = 128 from d = 768 (60.0 -> 59.0; d = 1024: 79.3 -> 77.0);
+// they keep one form, the contiguous runs.  Only the tile edges in TILES, the layouts in VARS and the
 // epilogues in EPIS are compiled (the host checks every problem).
 template <unsigned TILES, int W, unsigned VARS, unsigned EPIS, bool SHARES>
 __device__ __forceinline__ void panel_tile(const GemmBatch& bt, int t, float* smem) {
