@@ -716,22 +716,34 @@ __global__ __launch_bounds__(256) void input_update_kernel(
 
 // Blocks of the hot rows' launches; they take the parts (the rows) in turn.
 constexpr int kHotBlocks = 1024;
+// Parts times 64-column chunks up to which the parts are taken chunk by chunk: what
+// the blocks take in one turn.  At d = 500, 64 parts (16 384 slots on one row): 26
+// us for the update, 36 with 512 columns a block; 157 parts (40 000 slots): 44, 39.
+constexpr int kHotNarrow = kHotBlocks;
 
 // One part: kPartSlots slots of a hot row, in order, 64 to each wave; the four
 // sums are added in wave order.  The row itself is updated if this is all of it.
+// A block takes 512 columns of it, eight rows of dA in flight, or, when the parts
+// are too few to fill the chip so, 64 columns with all of a wave's 64 rows in
+// flight: the same sums.  (2049 slots on 16 rows, the whole update: 18 us at d =
+// 2048, 48 when a block took all columns of a part; d = 500: 18, 23.)
 template <int SB, bool VEC>
 __global__ __launch_bounds__(256) void input_hot_kernel(
     float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
     const uint2* spair, const int* rlen, const int* piv, int* multi, const int4* part, float* psum,
     const int* flags) {
   __shared__ float4 sums[3][2][64];
+  __shared__ float sums1[3][64];
   __shared__ int s_off[64], s_q[64];
   const int nb = (n + SB - 1) / SB;
   const int w = wave_index(), lane = threadIdx.x & 63;
   if (blockIdx.x == 0 && threadIdx.x == 0) multi[0] = 0;  // its rows are done
   const int count = *flags != 0 ? 0 : part[0].x;
-  for (int b = blockIdx.x; b < count; b += gridDim.x) {
-    const int4 pt = part[1 + b];
+  const bool narrow = count * ((d + 63) / 64) <= kHotNarrow;
+  const int cw = narrow ? 64 : 512, nch = (d + cw - 1) / cw;
+  for (int b = blockIdx.x; b < count * nch; b += gridDim.x) {
+    const int4 pt = part[1 + b / nch];
+    const int cg = b % nch * cw;
     const int r = __builtin_amdgcn_readfirstlane(pt.x), j = __builtin_amdgcn_readfirstlane(pt.y),
               total = __builtin_amdgcn_readfirstlane(pt.z),
               sum0 = __builtin_amdgcn_readfirstlane(pt.w);
@@ -741,6 +753,17 @@ __global__ __launch_bounds__(256) void input_hot_kernel(
       s_off[lane] = wave_prefix(mine, all);
       s_q[lane] = q;
     }
+    const bool whole = total <= kPartSlots;
+    float* out = whole ? W + (size_t)r * d : psum + (size_t)(sum0 + j) * d;
+    const int col = cg + lane, colc = min(col, d - 1);  // narrow
+    float old1 = 0.f;
+    float4 old[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      old[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (!narrow && w == 0 && whole) old[c] = row_load4<VEC>(out, cg + 256 * c + 4 * lane, d);
+    }
+    if (narrow && w == 0 && whole) old1 = out[colc];
     __syncthreads();
     const int tb = j * kPartSlots + 64 * w, te = min(total, tb + 64);
     uint2 x = make_uint2(0u, 0u);
@@ -752,15 +775,20 @@ __global__ __launch_bounds__(256) void input_hot_kernel(
         if (s_off[lo + s] <= t) lo += s;
       x = spair[s_q[lo] + t - s_off[lo]];
     }
-    const bool whole = total <= kPartSlots;
-    float* out = whole ? W + (size_t)r * d : psum + (size_t)(sum0 + j) * d;
-    for (int cg = 0; cg < d; cg += 512) {
-      float4 acc[2], old[2];
+    if (narrow) {
+      float acc = 0.f;
+      if (tb < te) acc = sum_list_col(gA, colc, te - tb, __uint_as_float(x.y), x.x);
+      if (w > 0) sums1[w - 1][lane] = acc;
+      __syncthreads();
+      if (w == 0) {
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        acc[c] = old[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (w == 0 && whole) old[c] = row_load4<VEC>(out, cg + 256 * c + 4 * lane, d);
+        for (int v = 0; v < 3; ++v) acc += sums1[v][lane];
+        if (col < d) out[col] = whole ? old1 - lr * acc : acc;
       }
+    } else {
+      float4 acc[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (tb < te) sum_list<VEC>(gA, d, cg, te - tb, __uint_as_float(x.y), x.x, acc);
       if (w > 0) {
         sums[w - 1][0][lane] = acc[0];
@@ -782,8 +810,8 @@ __global__ __launch_bounds__(256) void input_hot_kernel(
           row_store4<VEC>(out, cg + 256 * c + 4 * lane, d, acc[c]);
         }
       }
-      __syncthreads();
     }
+    __syncthreads();
   }
 }
 
@@ -943,8 +971,9 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
                        dim3((unsigned)(multi_blocks + nb * SB / (4 * kRunsPerWave))), dim3(256), 0,
                        s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair, s->rlen, s->rent,
                        s->piv, s->table, s->multi, s->part, s->split, s->flags, multi_blocks);
-    hipLaunchKernelGGL((input_hot_kernel<SB, VEC>), dim3((unsigned)std::min(parts, kHotBlocks)),
-                       dim3(256), 0, s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair,
+    hipLaunchKernelGGL((input_hot_kernel<SB, VEC>),
+                       dim3((unsigned)std::min(parts * ((s->d + 63) / 64), kHotBlocks)), dim3(256),
+                       0, s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair,
                        s->rlen, s->piv, s->multi, s->part, s->psum, s->flags);
   };
   constexpr std::integral_constant<int, kSortSmall> small_block{};
