@@ -81,13 +81,13 @@ static_assert(kInputHashSize >= 2 * kInputMaxSlots, "the row table must stay hal
 // one row is the grouped form faster (2048 slots: 52 and 22 us), which the host
 // cannot see.
 constexpr int kInputSmall = 2048;
-// Slots sorted by one block: 256 while that gives at most a block per lane of a
-// wave, else 1024.  The sort is a chain of exchanges, 36 stages for 256 and 55
-// for 1024, whose waves share a compute unit: 2049 slots at d = 500, the whole
-// update, 17 us with blocks of 256 and 24 with 1024; 16 384 slots 31 and 40.
-constexpr int kSortSmall = 256, kSortLarge = 1024;
-constexpr int kSortSmallSlots = 64 * kSortSmall;
-static_assert(kInputMaxSlots / kSortLarge <= 64, "a lane of a wave per sorted block");
+// Slots sorted by one block: 256, 512 or 1024, the fewest that give at most a block
+// per lane of a wave.  The sort is a chain of exchanges, 36, 45 or 55 stages, whose
+// waves share a compute unit: 2049 slots at d = 500, the whole update, 17 us with
+// blocks of 256 and 24 with 1024; 16 384 slots 31 and 40; 16 385 slots of 200 rows,
+// d = 32: 21 with 512 and 23 with 1024.
+constexpr int kMaxSorted = 64;  // sorted blocks
+static_assert(kInputMaxSlots <= kMaxSorted * 1024, "a lane of a wave per sorted block");
 // Rows of this many slots or more are not left to one wave.
 constexpr int kInputHotSlots = 64;
 constexpr int kPartSlots = 256;  // slots of a hot row that one block sums
@@ -425,24 +425,24 @@ __device__ __forceinline__ unsigned lane_xor(unsigned v) {
 // Ascending order of one key per thread over a block of SB threads (bitonic;
 // strides below 64 between lanes, by DPP and lane swaps, which do not go through
 // the LDS unit as shuffles do; the others through LDS).
-template <int SB, int KK, int J>
-__device__ __forceinline__ void sort_stages(unsigned long long& x, unsigned long long* sh) {
+template <int SB, int KK, int J, int P>
+__device__ __forceinline__ void sort_stages(unsigned long long& x, unsigned long long (*sh)[SB]) {
   const int t = threadIdx.x;
   unsigned long long o;
-  if constexpr (J >= 64) {
-    sh[t] = x;
+  if constexpr (J >= 64) {  // (two buffers in turn: one barrier a stage)
+    sh[P][t] = x;
     __syncthreads();
-    o = sh[t ^ J];
-    __syncthreads();
+    o = sh[P][t ^ J];
   } else {
     o = ((unsigned long long)lane_xor<J>((unsigned)(x >> 32)) << 32) | lane_xor<J>((unsigned)x);
   }
   const bool up = (t & KK) == 0, low = (t & J) == 0;
   x = (low == up) == (o < x) ? o : x;  // (keys are distinct)
+  constexpr int Q = J >= 64 ? P ^ 1 : P;
   if constexpr (J > 1)
-    sort_stages<SB, KK, J / 2>(x, sh);
+    sort_stages<SB, KK, J / 2, Q>(x, sh);
   else if constexpr (KK < SB)
-    sort_stages<SB, 2 * KK, KK>(x, sh);
+    sort_stages<SB, 2 * KK, KK, Q>(x, sh);
 }
 
 // Block b sorts slots [SB b, +SB) by (row, slot) and counts each run in the
@@ -452,7 +452,7 @@ __global__ __launch_bounds__(SB) void input_group_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ val, int n, int K, int d, int64_t D,
     int* srow, uint2* spair, int* rlen, int* rent, int* piv, unsigned long long* table,
     int* multi, int4* part, int* flags) {
-  __shared__ unsigned long long sh[SB];
+  __shared__ unsigned long long bufs[2][SB];
   __shared__ unsigned long long heads[SB / 64];
   __shared__ float vals[SB];
   const int t = threadIdx.x, e = blockIdx.x * SB + t;
@@ -463,7 +463,9 @@ __global__ __launch_bounds__(SB) void input_group_kernel(
   const bool valid = r >= 0 && (int64_t)r < D;
   const unsigned row = valid ? (unsigned)r : 0xffffffffu;  // the others last
   unsigned long long x = ((unsigned long long)row << 32) | (unsigned)e;
-  sort_stages<SB, 2, 1>(x, sh);
+  sort_stages<SB, 2, 1, 0>(x, bufs);
+  __syncthreads();
+  unsigned long long* sh = bufs[0];
   sh[t] = x;
   __syncthreads();
   const unsigned my = (unsigned)(x >> 32);
@@ -559,10 +561,13 @@ __device__ __forceinline__ int wave_prefix(int v, int& total) {
   return s - v;
 }
 
-// Sorted positions of one wave: their runs are looked up together, one a lane.
-// 4: at the largest Zipf 1.1 call 81 us for update and forward pass, 92 at 16
-// (too few waves for the rows of one slot); with uniform rows 126, 155 at 1.
-constexpr int kRunsPerWave = 4;
+// Sorted positions of one wave: their runs are looked up together, one a lane.  4
+// for large calls (the largest Zipf 1.1 call, update and forward pass: 81 us, 92 at
+// 16, with too few waves for the rows of one slot; uniform rows 126, 155 at 1); 1 up
+// to 16 384 slots, whose runs are too few to fill the chip (4096 slots in pairs, d =
+// 2048: 22 us, 24 at 4; 16 384 at d = 500: 22, 21).
+template <int SB>
+constexpr int kRunsPerWave = SB == 256 ? 1 : 4;
 // Blocks (of four waves) for the rows that several blocks name, at most (and no
 // more than a wave per such row).
 constexpr int kMultiBlocks = 1024;
@@ -586,19 +591,19 @@ __device__ __forceinline__ void list_parts(int row, int total, int4* part, int4*
   for (int j = lane; j < np; j += 64) part[at + j] = make_int4(row, j, total, sum);
 }
 
-// Positions [p0, p0 + kRunsPerWave): the runs whose row no other block names.
-template <bool VEC>
+// Positions [p0, p0 + R): the runs whose row no other block names.
+template <int R, bool VEC>
 __device__ __forceinline__ void update_runs(float* W, const float* gA, int d, float lr, int p0,
                                             const int* srow, const uint2* spair, const int* rlen,
                                             const int* rent, unsigned long long* table, int4* part,
                                             int4* split, int pending) {
   const int lane = threadIdx.x & 63;
-  const int p = p0 + min(lane, kRunsPerWave - 1);
+  const int p = p0 + min(lane, R - 1);
   int len = rlen[p];
   const int r = srow[p], h = rent[p];
   const uint2 pr = spair[p];
   bool mine = false;
-  if (lane < kRunsPerWave && len > 0 && h >= 0) {
+  if (lane < R && len > 0 && h >= 0) {
     if ((unsigned)table[h] == 1u) {
       mine = true;
       table[h] = kNoEntry;
@@ -679,9 +684,9 @@ __global__ __launch_bounds__(256) void input_update_kernel(
   const int nb = (n + SB - 1) / SB;
   const int pending = *flags;
   if ((int)blockIdx.x >= multi_blocks) {
-    const int p0 = (((int)blockIdx.x - multi_blocks) * 4 + w) * kRunsPerWave;
+    const int p0 = (((int)blockIdx.x - multi_blocks) * 4 + w) * kRunsPerWave<SB>;
     if (p0 >= nb * SB) return;
-    update_runs<VEC>(W, gA, d, lr, p0, srow, spair, rlen, rent, table, part, split, pending);
+    update_runs<kRunsPerWave<SB>, VEC>(W, gA, d, lr, p0, srow, spair, rlen, rent, table, part, split, pending);
     return;
   }
   // The listed rows wv, wv + nw, ...: one a lane, then one after another.
@@ -968,7 +973,7 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
                        s->part, s->flags);
     const int multi_blocks = std::min(kMultiBlocks, (n / 2 + 3) / 4);
     hipLaunchKernelGGL((input_update_kernel<SB, VEC>),
-                       dim3((unsigned)(multi_blocks + nb * SB / (4 * kRunsPerWave))), dim3(256), 0,
+                       dim3((unsigned)(multi_blocks + nb * SB / (4 * kRunsPerWave<SB>))), dim3(256), 0,
                        s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair, s->rlen, s->rent,
                        s->piv, s->table, s->multi, s->part, s->split, s->flags, multi_blocks);
     hipLaunchKernelGGL((input_hot_kernel<SB, VEC>),
@@ -976,12 +981,12 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
                        0, s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair,
                        s->rlen, s->piv, s->multi, s->part, s->psum, s->flags);
   };
-  constexpr std::integral_constant<int, kSortSmall> small_block{};
-  constexpr std::integral_constant<int, kSortLarge> large_block{};
-  if (n <= kSortSmallSlots)
-    vec ? grouped(small_block, std::true_type{}) : grouped(small_block, std::false_type{});
-  else
-    vec ? grouped(large_block, std::true_type{}) : grouped(large_block, std::false_type{});
+  auto blocks_of = [&](auto block) {
+    vec ? grouped(block, std::true_type{}) : grouped(block, std::false_type{});
+  };
+  if (n <= 256 * kMaxSorted) blocks_of(std::integral_constant<int, 256>{});
+  else if (n <= 512 * kMaxSorted) blocks_of(std::integral_constant<int, 512>{});
+  else blocks_of(std::integral_constant<int, 1024>{});
   const int most = (n / kPartSlots) * ((s->d + 63) / 64);
   hipLaunchKernelGGL(input_split_kernel, dim3((unsigned)std::min((most + 3) / 4, kHotBlocks)),
                      dim3(256), 0, s->stream, s->W, s->d, lr, s->part, s->split, s->psum,
