@@ -46,23 +46,9 @@ struct lst_input {
   hipStream_t stream = nullptr;
   float* W = nullptr;
   int* flags = nullptr;  // [0]: sticky status
-  // open-addressing table of the rows of one large update (empty between
-  // calls): row in the upper, number of runs in the lower 32 bits
-  unsigned long long* table = nullptr;
-  // per sorted position: row, pair (offset of the example's row of dA, value),
-  // length of the run that starts there (0: none does) and the run's table
-  // entry
-  int* srow = nullptr;
-  uint2* spair = nullptr;
-  int* rlen = nullptr;
-  int* rent = nullptr;
-  int* piv = nullptr;    // the last row of each 64 positions, then of each 16
-  int* multi = nullptr;  // table entries of the rows several blocks name ([0]: count)
-  // parts of the rows of at least kInputHotSlots slots: [0] = (parts, rows of
-  // several parts, sums taken of psum), then (row, part, slots of the row, the
-  // row's first sum in psum); the rows of several parts; and the sums
-  int4* part = nullptr;
-  int4* split = nullptr;
+  // workspace of one large update (InputWs)
+  unsigned char* ws = nullptr;
+  unsigned char* sorted = nullptr;
   float* psum = nullptr;
 };
 
@@ -95,6 +81,57 @@ constexpr int kMaxParts = kInputMaxSlots / kInputHotSlots + kInputMaxSlots / kPa
 constexpr int kMaxSplit = kInputMaxSlots / kPartSlots;     // rows of several parts
 constexpr int kMaxSums = 2 * kInputMaxSlots / kPartSlots;  // their parts
 
+// The workspace of one large update, in three allocations: three pointers are what
+// its launches pass (the host spends time on every byte of kernel arguments: with
+// every array by itself, the update of 2049 slots at d = 500 took 17 us, 13 to 16
+// so), and allocations below 2 MB are the cheap ones (one of 2.5 MB made
+// lst_input_init 8 us longer).
+struct InputWs {
+  unsigned char* p;
+  // open-addressing table of the rows (empty between calls): row in the upper,
+  // number of runs in the lower 32 bits
+  static constexpr size_t kTable = 0;
+  // parts of the rows of at least kInputHotSlots slots: [0] = (parts, rows of
+  // several parts, sums taken of psum), then (row, part, slots of the row, the
+  // row's first sum in psum); and the rows of several parts
+  static constexpr size_t kPart = kTable + kInputHashSize * sizeof(unsigned long long);
+  static constexpr size_t kSplit = kPart + (1 + kMaxParts) * sizeof(int4);
+  // the last sorted row of each 64 positions, then of each 16
+  static constexpr size_t kPiv = kSplit + kMaxSplit * sizeof(int4);
+  // table entries of the rows several blocks name ([0]: count)
+  static constexpr size_t kMulti = kPiv + (kInputMaxSlots / 64 + kInputMaxSlots / 16) * sizeof(int);
+  static constexpr size_t kBytes = kMulti + (1 + kInputMaxSlots / 2) * sizeof(int);
+
+  unsigned char* sorted;
+  // per sorted position: pair (offset of the example's row of dA, value), row,
+  // length of the run that starts there (0: none does) and the run's table entry
+  static constexpr size_t kPair = 0;
+  static constexpr size_t kRow = kPair + kInputMaxSlots * sizeof(uint2);
+  static constexpr size_t kLen = kRow + kInputMaxSlots * sizeof(int);
+  static constexpr size_t kEnt = kLen + kInputMaxSlots * sizeof(int);
+  static constexpr size_t kSortedBytes = kEnt + kInputMaxSlots * sizeof(int);
+
+  float* psum;  // the sums of the rows of several parts, kMaxSums rows of d
+
+  template <class T>
+  __device__ __forceinline__ static T* at(unsigned char* base, size_t off) {
+    return reinterpret_cast<T*>(base + off);
+  }
+  __device__ __forceinline__ unsigned long long* table() const {
+    return at<unsigned long long>(p, kTable);
+  }
+  __device__ __forceinline__ int4* part() const { return at<int4>(p, kPart); }
+  __device__ __forceinline__ int4* split() const { return at<int4>(p, kSplit); }
+  __device__ __forceinline__ int* piv() const { return at<int>(p, kPiv); }
+  __device__ __forceinline__ int* multi() const { return at<int>(p, kMulti); }
+  __device__ __forceinline__ uint2* spair() const { return at<uint2>(sorted, kPair); }
+  __device__ __forceinline__ int* srow() const { return at<int>(sorted, kRow); }
+  __device__ __forceinline__ int* rlen() const { return at<int>(sorted, kLen); }
+  __device__ __forceinline__ int* rent() const { return at<int>(sorted, kEnt); }
+};
+static_assert(InputWs::kPart % 16 == 0 && InputWs::kPiv % 16 == 0 && InputWs::kRow % 16 == 0,
+              "read in pieces of 16 bytes");
+
 __device__ __forceinline__ unsigned input_hash(int r) {
   return ((unsigned)r * 2654435761u) >> (32 - kInputHashBits);
 }
@@ -102,10 +139,10 @@ __device__ __forceinline__ unsigned input_hash(int r) {
 // An empty table entry (no row is 0x7fffffff or above).
 constexpr unsigned long long kNoEntry = ~0ull;
 
-__global__ void input_table_init_kernel(unsigned long long* table, int* multi) {
+__global__ void input_table_init_kernel(InputWs ws) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e == 0) multi[0] = 0;
-  if (e < kInputHashSize) table[e] = kNoEntry;
+  if (e == 0) ws.multi()[0] = 0;
+  if (e < kInputHashSize) ws.table()[e] = kNoEntry;
 }
 
 // The wave's number in its block, in a scalar register: what depends on it
@@ -450,13 +487,14 @@ __device__ __forceinline__ void sort_stages(unsigned long long& x, unsigned long
 template <int SB>
 __global__ __launch_bounds__(SB) void input_group_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ val, int n, int K, int d, int64_t D,
-    int* srow, uint2* spair, int* rlen, int* rent, int* piv, unsigned long long* table,
-    int* multi, int4* part, int* flags) {
+    InputWs ws, int* flags) {
   __shared__ unsigned long long bufs[2][SB];
   __shared__ unsigned long long heads[SB / 64];
   __shared__ float vals[SB];
   const int t = threadIdx.x, e = blockIdx.x * SB + t;
-  if (e == 0) part[0] = make_int4(0, 0, 0, 0);
+  unsigned long long* table = ws.table();
+  int *piv = ws.piv(), *multi = ws.multi();
+  if (e == 0) ws.part()[0] = make_int4(0, 0, 0, 0);
   const int r = e < n ? idx[e] : -1;
   vals[t] = e < n ? val[e] : 0.f;
   if (r < -1 || (int64_t)r >= D) atomicCAS(flags, 0, LST_EINDEX);
@@ -492,9 +530,9 @@ __global__ __launch_bounds__(SB) void input_group_kernel(
   }
   // the position's arrays are whole blocks (kInputMaxSlots is a multiple of SB)
   const int row_out = end ? 0x7fffffff : (int)my;
-  srow[e] = row_out;
-  spair[e] = make_uint2((unsigned)(slot / K) * (unsigned)d, __float_as_uint(v));
-  rlen[e] = len;
+  ws.srow()[e] = row_out;
+  ws.spair()[e] = make_uint2((unsigned)(slot / K) * (unsigned)d, __float_as_uint(v));
+  ws.rlen()[e] = len;
   if ((t & 63) == 63) piv[e >> 6] = row_out;
   if ((t & 15) == 15) piv[kInputMaxSlots / 64 + (e >> 4)] = row_out;
   if (head) {
@@ -512,7 +550,7 @@ __global__ __launch_bounds__(SB) void input_group_kernel(
       h = (h + 1) & (kInputHashSize - 1);
     }
   }
-  rent[e] = ent;
+  ws.rent()[e] = ent;
 }
 
 // Block b's run of row r: its first position in q, its length returned (0:
@@ -521,11 +559,11 @@ __device__ __forceinline__ int below(const int4& x, int r) {
   return (x.x < r) + (x.y < r) + (x.z < r) + (x.w < r);
 }
 template <int SB>
-__device__ __forceinline__ int find_run(const int* srow, const int* rlen, const int* piv, int b,
-                                        int nb, int r, int& q) {
+__device__ __forceinline__ int find_run(const InputWs& ws, int b, int nb, int r, int& q) {
   q = 0;
   if (b >= nb) return 0;
   constexpr int kGroups = SB / 64;
+  const int* piv = ws.piv();
   const int4* p64 = reinterpret_cast<const int4*>(piv + b * kGroups);
   int grp = 0;
 #pragma unroll
@@ -534,7 +572,7 @@ __device__ __forceinline__ int find_run(const int* srow, const int* rlen, const 
   grp += b * kGroups;
   const int sub =
       4 * grp + below(reinterpret_cast<const int4*>(piv + kInputMaxSlots / 64)[grp], r);
-  const int4* sr = reinterpret_cast<const int4*>(srow + 16 * sub);
+  const int4* sr = reinterpret_cast<const int4*>(ws.srow() + 16 * sub);
   int lt = 0;
   bool eq = false;
 #pragma unroll
@@ -545,7 +583,7 @@ __device__ __forceinline__ int find_run(const int* srow, const int* rlen, const 
   }
   if (!eq) return 0;
   q = 16 * sub + lt;
-  return rlen[q];
+  return ws.rlen()[q];
 }
 
 // Exclusive prefix sum over the wave (every lane takes part); total in all lanes.
@@ -575,7 +613,8 @@ static_assert(kInputMaxSlots / 2 <= 4 * kMultiBlocks * 64, "a lane for each of a
 
 // Lists the parts of a row of total (>= kInputHotSlots) slots; every lane of
 // the wave takes part.
-__device__ __forceinline__ void list_parts(int row, int total, int4* part, int4* split) {
+__device__ __forceinline__ void list_parts(const InputWs& ws, int row, int total) {
+  int4 *part = ws.part(), *split = ws.split();
   const int lane = threadIdx.x & 63;
   const int np = (total + kPartSlots - 1) / kPartSlots;
   int at = 0, sum = 0;
@@ -594,13 +633,13 @@ __device__ __forceinline__ void list_parts(int row, int total, int4* part, int4*
 // Positions [p0, p0 + R): the runs whose row no other block names.
 template <int R, bool VEC>
 __device__ __forceinline__ void update_runs(float* W, const float* gA, int d, float lr, int p0,
-                                            const int* srow, const uint2* spair, const int* rlen,
-                                            const int* rent, unsigned long long* table, int4* part,
-                                            int4* split, int pending) {
+                                            const InputWs& ws, int pending) {
+  unsigned long long* table = ws.table();
+  const uint2* spair = ws.spair();
   const int lane = threadIdx.x & 63;
   const int p = p0 + min(lane, R - 1);
-  int len = rlen[p];
-  const int r = srow[p], h = rent[p];
+  int len = ws.rlen()[p];
+  const int r = ws.srow()[p], h = ws.rent()[p];
   const uint2 pr = spair[p];
   bool mine = false;
   if (lane < R && len > 0 && h >= 0) {
@@ -614,7 +653,7 @@ __device__ __forceinline__ void update_runs(float* W, const float* gA, int d, fl
   while (many != 0ull) {
     const int l = __ffsll((unsigned long long)many) - 1;
     many &= many - 1;
-    list_parts(__builtin_amdgcn_readlane(r, l), __builtin_amdgcn_readlane(len, l), part, split);
+    list_parts(ws, __builtin_amdgcn_readlane(r, l), __builtin_amdgcn_readlane(len, l));
   }
   // rows of one slot, kListRows / 2 at a time
   unsigned long long todo = __ballot(mine && len == 1);
@@ -674,11 +713,10 @@ __device__ __forceinline__ void update_runs(float* W, const float* gA, int d, fl
 }
 
 template <int SB, bool VEC>
-__global__ __launch_bounds__(256) void input_update_kernel(
-    float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
-    const uint2* spair, const int* rlen, const int* rent, const int* piv,
-    unsigned long long* table, const int* multi, int4* part, int4* split, const int* flags,
-    int multi_blocks) {
+__global__ __launch_bounds__(256) void input_update_kernel(float* __restrict__ W, int d,
+                                                           const float* __restrict__ gA, int n,
+                                                           float lr, InputWs ws, const int* flags,
+                                                           int multi_blocks) {
   __shared__ uint2 list[4][kInputHotSlots];
   const int w = wave_index(), lane = threadIdx.x & 63;
   const int nb = (n + SB - 1) / SB;
@@ -686,11 +724,14 @@ __global__ __launch_bounds__(256) void input_update_kernel(
   if ((int)blockIdx.x >= multi_blocks) {
     const int p0 = (((int)blockIdx.x - multi_blocks) * 4 + w) * kRunsPerWave<SB>;
     if (p0 >= nb * SB) return;
-    update_runs<kRunsPerWave<SB>, VEC>(W, gA, d, lr, p0, srow, spair, rlen, rent, table, part, split, pending);
+    update_runs<kRunsPerWave<SB>, VEC>(W, gA, d, lr, p0, ws, pending);
     return;
   }
   // The listed rows wv, wv + nw, ...: one a lane, then one after another.
   const int wv = (int)blockIdx.x * 4 + w, nw = 4 * multi_blocks;
+  unsigned long long* table = ws.table();
+  const uint2* spair = ws.spair();
+  const int* multi = ws.multi();
   const int count = multi[0];
   const int at = wv + nw * lane;
   int row = -1;
@@ -703,10 +744,10 @@ __global__ __launch_bounds__(256) void input_update_kernel(
   for (int l = 0; wv + nw * l < count; ++l) {
     const int r = __builtin_amdgcn_readlane(row, l);
     int q, total;
-    const int mine = find_run<SB>(srow, rlen, piv, lane, nb, r, q);
+    const int mine = find_run<SB>(ws, lane, nb, r, q);
     const int off = wave_prefix(mine, total);
     if (total >= kInputHotSlots) {
-      list_parts(r, total, part, split);
+      list_parts(ws, r, total);
       continue;
     }
     for (int u = 0; u < mine; ++u) list[w][off + u] = spair[q + u];
@@ -733,16 +774,17 @@ constexpr int kHotNarrow = kHotBlocks;
 // flight: the same sums.  (2049 slots on 16 rows, the whole update: 18 us at d =
 // 2048, 48 when a block took all columns of a part; d = 500: 18, 23.)
 template <int SB, bool VEC>
-__global__ __launch_bounds__(256) void input_hot_kernel(
-    float* __restrict__ W, int d, const float* __restrict__ gA, int n, float lr, const int* srow,
-    const uint2* spair, const int* rlen, const int* piv, int* multi, const int4* part, float* psum,
-    const int* flags) {
+__global__ __launch_bounds__(256) void input_hot_kernel(float* __restrict__ W, int d,
+                                                        const float* __restrict__ gA, int n,
+                                                        float lr, InputWs ws, const int* flags) {
   __shared__ float4 sums[3][2][64];
   __shared__ float sums1[3][64];
   __shared__ int s_off[64], s_q[64];
   const int nb = (n + SB - 1) / SB;
   const int w = wave_index(), lane = threadIdx.x & 63;
-  if (blockIdx.x == 0 && threadIdx.x == 0) multi[0] = 0;  // its rows are done
+  const int4* part = ws.part();
+  const uint2* spair = ws.spair();
+  if (blockIdx.x == 0 && threadIdx.x == 0) ws.multi()[0] = 0;  // its rows are done
   const int count = *flags != 0 ? 0 : part[0].x;
   const bool narrow = count * ((d + 63) / 64) <= kHotNarrow;
   const int cw = narrow ? 64 : 512, nch = (d + cw - 1) / cw;
@@ -754,12 +796,12 @@ __global__ __launch_bounds__(256) void input_hot_kernel(
               sum0 = __builtin_amdgcn_readfirstlane(pt.w);
     if (w == 0) {
       int q, all;
-      const int mine = find_run<SB>(srow, rlen, piv, lane, nb, r, q);
+      const int mine = find_run<SB>(ws, lane, nb, r, q);
       s_off[lane] = wave_prefix(mine, all);
       s_q[lane] = q;
     }
     const bool whole = total <= kPartSlots;
-    float* out = whole ? W + (size_t)r * d : psum + (size_t)(sum0 + j) * d;
+    float* out = whole ? W + (size_t)r * d : ws.psum + (size_t)(sum0 + j) * d;
     const int col = cg + lane, colc = min(col, d - 1);  // narrow
     float old1 = 0.f;
     float4 old[2];
@@ -823,17 +865,16 @@ __global__ __launch_bounds__(256) void input_hot_kernel(
 // Rows of several parts: a wave per (row, 64 columns) adds the parts' sums in
 // order, sixteen in flight, and updates the row.
 __global__ __launch_bounds__(256) void input_split_kernel(float* __restrict__ W, int d, float lr,
-                                                          const int4* part, const int4* split,
-                                                          const float* psum, const int* flags) {
+                                                          InputWs ws, const int* flags) {
   const int nch = (d + 63) / 64;
   const int w = wave_index(), lane = threadIdx.x & 63;
-  const int count = *flags != 0 ? 0 : part[0].y;
+  const int count = *flags != 0 ? 0 : ws.part()[0].y;
   for (int b = (int)blockIdx.x * 4 + w; b < count * nch; b += 4 * gridDim.x) {
-    const int4 sp = split[b / nch];
+    const int4 sp = ws.split()[b / nch];
     const int col = (b % nch) * 64 + lane, colc = min(col, d - 1), np = sp.z;
     float* out = W + (size_t)sp.x * d + colc;
     const float old = *out;
-    const float* ps = psum + (size_t)sp.y * d + colc;
+    const float* ps = ws.psum + (size_t)sp.y * d + colc;
     float acc = 0.f;
     for (int j0 = 0; j0 < np; j0 += 16) {
       float g[16];
@@ -882,9 +923,8 @@ int lst_input_init(lst_input** out, int64_t D_in, int32_t d, const float* W_in,
   s->stream = static_cast<hipStream_t>(hip_stream);
   auto fail = [&](int code) {
     (void)hipStreamSynchronize(s->stream);
-    for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->table,
-                    (void*)s->srow, (void*)s->spair, (void*)s->rlen, (void*)s->rent,
-                    (void*)s->piv, (void*)s->multi, (void*)s->part, (void*)s->split, (void*)s->psum})
+    for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->ws, (void*)s->sorted,
+                    (void*)s->psum})
       if (p) (void)hipFree(p);
     delete s;
     return code;
@@ -892,19 +932,12 @@ int lst_input_init(lst_input** out, int64_t D_in, int32_t d, const float* W_in,
   if (hipGetDevice(&s->device) != hipSuccess) return fail(LST_EHIP);
   if (hipMalloc((void**)&s->W, (size_t)D_in * d * sizeof(float)) != hipSuccess ||
       hipMalloc((void**)&s->flags, sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->table, kInputHashSize * sizeof(unsigned long long)) != hipSuccess ||
-      hipMalloc((void**)&s->srow, kInputMaxSlots * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->spair, kInputMaxSlots * sizeof(uint2)) != hipSuccess ||
-      hipMalloc((void**)&s->piv, (kInputMaxSlots / 64 + kInputMaxSlots / 16) * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->multi, (1 + kInputMaxSlots / 2) * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->rlen, kInputMaxSlots * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->rent, kInputMaxSlots * sizeof(int)) != hipSuccess ||
-      hipMalloc((void**)&s->part, (1 + kMaxParts) * sizeof(int4)) != hipSuccess ||
-      hipMalloc((void**)&s->split, kMaxSplit * sizeof(int4)) != hipSuccess ||
+      hipMalloc((void**)&s->ws, InputWs::kBytes) != hipSuccess ||
+      hipMalloc((void**)&s->sorted, InputWs::kSortedBytes) != hipSuccess ||
       hipMalloc((void**)&s->psum, (size_t)kMaxSums * d * sizeof(float)) != hipSuccess)
     return fail(LST_ENOMEM);
   hipLaunchKernelGGL(input_table_init_kernel, dim3(kInputHashSize / 256), dim3(256), 0, s->stream,
-                     s->table, s->multi);
+                     InputWs{s->ws, s->sorted, s->psum});
   if (hipMemsetAsync(s->flags, 0, sizeof(int), s->stream) != hipSuccess ||
       hipMemcpyAsync(s->W, W_in, (size_t)D_in * d * sizeof(float), hipMemcpyDeviceToDevice,
                      s->stream) != hipSuccess ||
@@ -964,22 +997,21 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
     return hipGetLastError() == hipSuccess ? LST_OK : LST_EHIP;
   }
   const int parts = n / kInputHotSlots + n / kPartSlots;  // at most
+  const InputWs ws{s->ws, s->sorted, s->psum};
   auto grouped = [&](auto block, auto vec16) {
     constexpr int SB = decltype(block)::value;
     constexpr bool VEC = decltype(vec16)::value;
     const int nb = (n + SB - 1) / SB;
     hipLaunchKernelGGL(input_group_kernel<SB>, dim3(nb), dim3(SB), 0, s->stream, idx, val, n, K,
-                       s->d, s->D, s->srow, s->spair, s->rlen, s->rent, s->piv, s->table, s->multi,
-                       s->part, s->flags);
+                       s->d, s->D, ws, s->flags);
     const int multi_blocks = std::min(kMultiBlocks, (n / 2 + 3) / 4);
     hipLaunchKernelGGL((input_update_kernel<SB, VEC>),
-                       dim3((unsigned)(multi_blocks + nb * SB / (4 * kRunsPerWave<SB>))), dim3(256), 0,
-                       s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair, s->rlen, s->rent,
-                       s->piv, s->table, s->multi, s->part, s->split, s->flags, multi_blocks);
+                       dim3((unsigned)(multi_blocks + nb * SB / (4 * kRunsPerWave<SB>))),
+                       dim3(256), 0, s->stream, s->W, s->d, grad_A, n, lr, ws, s->flags,
+                       multi_blocks);
     hipLaunchKernelGGL((input_hot_kernel<SB, VEC>),
                        dim3((unsigned)std::min(parts * ((s->d + 63) / 64), kHotBlocks)), dim3(256),
-                       0, s->stream, s->W, s->d, grad_A, n, lr, s->srow, s->spair,
-                       s->rlen, s->piv, s->multi, s->part, s->psum, s->flags);
+                       0, s->stream, s->W, s->d, grad_A, n, lr, ws, s->flags);
   };
   auto blocks_of = [&](auto block) {
     vec ? grouped(block, std::true_type{}) : grouped(block, std::false_type{});
@@ -989,8 +1021,7 @@ int lst_input_update(lst_input* s, int32_t m, int32_t K, const int32_t* idx, con
   else blocks_of(std::integral_constant<int, 1024>{});
   const int most = (n / kPartSlots) * ((s->d + 63) / 64);
   hipLaunchKernelGGL(input_split_kernel, dim3((unsigned)std::min((most + 3) / 4, kHotBlocks)),
-                     dim3(256), 0, s->stream, s->W, s->d, lr, s->part, s->split, s->psum,
-                     s->flags);
+                     dim3(256), 0, s->stream, s->W, s->d, lr, ws, s->flags);
   return hipGetLastError() == hipSuccess ? LST_OK : LST_EHIP;
 }
 
@@ -1022,9 +1053,8 @@ void lst_input_free(lst_input* s) {
   if (!s) return;
   DeviceScope g(s->device);
   (void)hipStreamSynchronize(s->stream);
-  for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->table,
-                  (void*)s->srow, (void*)s->spair, (void*)s->rlen, (void*)s->rent,
-                  (void*)s->piv, (void*)s->multi, (void*)s->part, (void*)s->split, (void*)s->psum})
+  for (void* p : {(void*)s->W, (void*)s->flags, (void*)s->ws, (void*)s->sorted,
+                  (void*)s->psum})
     (void)hipFree(p);
   delete s;
 }
