@@ -72,7 +72,7 @@ struct lst_state {
   int n_c1p = 0;  // partial sums of h^T Q h per example (two per 32-column tile of H^)
   int n_hap_max = 0;  // partial sums of |H^T H| per row for m = m_max
   // naive workspace
-  float* O = nullptr;      // m_max x ldo, zeros past column D
+  float* O = nullptr;      // m_max x ldo, zeros past column D once the row sums have run
   int64_t ldo = 0;
   float* wsplit = nullptr;
   double* nws = nullptr;  // row sums in chunks
@@ -278,7 +278,6 @@ int common_init(lst_state* s, int64_t D, int32_t d, const lst_config* cfg, void*
   s->stream = static_cast<hipStream_t>(hip_stream);
   HIPCHK(hipStreamCreateWithFlags(&s->cap, hipStreamNonBlocking));
   HIPCHK(configure_kernels());
-  HIPCHK(lu_configure());
   OK_OR_RETURN(scratch_device_ptr(s->device, &s->scratch));
   OK_OR_RETURN(dalloc(s, &s->flags, F_COUNT));
   HIPCHK(hipMemsetAsync(s->flags, 0, F_COUNT * sizeof(int), s->stream));
@@ -962,6 +961,7 @@ int lst_step_solve(lst_state* s, int32_t m, int32_t K, const float* H, const int
   if (s->kind != 0) return LST_ESTATE;
   if (s->d > kLuMaxD) return LST_EINVAL;
   DeviceGuard dg(s->device);
+  if (!s->lu_act) HIPCHK(lu_configure());
   {  // (each by itself: an earlier call may have run out of memory half way)
     const int d = s->d;
     if ((!s->lu_F && (rc = dalloc(s, &s->lu_F, (size_t)d * d))) ||
@@ -1120,10 +1120,6 @@ int lst_naive_init(lst_state** out, int64_t D, int32_t d, const float* W, const 
       (rc = dalloc(s, &s->wsplit, (size_t)ks * m * d)) ||
       (rc = dalloc(s, &s->nws, naive_ws_doubles(m))))
     return fail(rc);
-  if (s->ldo > D &&
-      hipMemset2DAsync(s->O + D, (size_t)s->ldo * sizeof(float), 0,
-                       (size_t)(s->ldo - D) * sizeof(float), (size_t)m, s->stream) != hipSuccess)
-    return fail(LST_EHIP);
   if (hipMemcpyAsync(s->V, W, (size_t)D * d * sizeof(float), hipMemcpyDeviceToDevice, s->stream) !=
       hipSuccess)
     return fail(LST_EHIP);
