@@ -263,6 +263,35 @@ def test_input_layer_order_of_sums(gpu_lib, pairs, d):
         layer.close()
 
 
+@pytest.mark.parametrize("pairs,d", [
+    ((32768,), 512),                                           # 128 parts of 8 chunks: narrow
+    ((32769,), 512),                                           # 129: 512 columns a block
+    ((24321,), 700),                                           # two of them
+    ((53000,), 301),                                           # rows not aligned
+    ((30000, 20000, 300, 256, 64, 63, 1), 330),                # rows of one part and of many
+])
+def test_input_layer_order_of_long_sums(gpu_lib, pairs, d):
+    """The same for the parts of hot rows on either side of the line (1024 parts times 64-column
+    chunks) from which a block takes 512 columns of a part."""
+    import torch
+
+    rng = np.random.default_rng(sum(pairs) + d)
+    m, K = 1024, 64
+    idx = np.full(m * K, -1, np.int32)
+    idx[rng.permutation(m * K)[:sum(pairs)]] = np.repeat(np.arange(len(pairs)), pairs)
+    idx = idx.reshape(m, K)
+    val = np.exp2(rng.integers(-2, 3, (m, K))).astype(np.float32)
+    G = rng.standard_normal((m, d)).astype(np.float32)
+    W = rng.standard_normal((len(pairs) + 1, d)).astype(np.float32)
+    layer = _layer(W)
+    layer.update(*(torch.from_numpy(x).cuda() for x in (idx, val, G)), 0.125)
+    assert layer.sync() == 0
+    got = layer.get_W().cpu().numpy()
+    layer.close()
+    want = _documented_update(W, idx, val, G, 0.125)
+    assert np.array_equal(got, want), np.abs(got - want).max(axis=1)
+
+
 @pytest.mark.parametrize("kw", [
     dict(m=1024, K=64, d=36, D=50),                            # every row of several parts
     dict(m=4096, K=16, d=20, D=30000, idx_dist="zipf", zipf_s=1.0),
