@@ -282,6 +282,18 @@ def test_naive_infinite_row(gpu_lib, D):
     assert torch.equal(l0[others], l1[others]) and torch.equal(g0[others], g1[others])
 
 
+@pytest.mark.parametrize("K,D", [(1, 3), (3, 50), (255, 40), (256, 2500), (257, 40), (300, 70001),
+                                 (1023, 3001), (1024, 2)])
+def test_naive_long_target_lists(gpu_lib, K, D):
+    """Targets subtracted by the first slot of their row: lists of a slot a thread (K = 256) and
+    of four, whole pieces of four keys and not, repeats and pads, in one chunk of the row and in
+    many."""
+    cfg = _cfg(D=D, d=20, m=5, K=K, lr=1e-5, distinct=False, dup_frac=0.3, pad_frac=0.2,
+               entropy=1200 + K + D)
+    reports, W_rel, _ = run_parity(cfg, 3, naive=True)
+    _assert(reports, W_rel, rows=False)
+
+
 @pytest.mark.parametrize("m,d,D", [(5, 4, 30), (30, 36, 997), (64, 100, 1030), (128, 132, 2001),
                                    (130, 260, 1500)])
 def test_naive_unaligned_rows(gpu_lib, m, d, D):
